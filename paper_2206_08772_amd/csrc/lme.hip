@@ -22,6 +22,7 @@
 // 1e-12 (1 + |log Z|), up to 30 halvings; stop at |r|_2 <= tol.  Gradients
 // dN_I = -N_I J^{-1} d_I at the converged multiplier.
 #include "launch.h"
+#include "lme.h"
 #include "otm_common.h"
 
 namespace otm {
@@ -42,27 +43,8 @@ OTM_DEV void node_xyz(const NodeSrc& s, int32_t I, double& a, double& b, double&
   }
 }
 
-// exp(x) for the shifted exponents of the LME weights (x <= 0 up to
-// rounding): Cody-Waite reduction x = k ln2 + r with ln2 split in a 32-bit
-// head and its remainder (k ln2_hi is exact), |r| <= ln2/2, then the Taylor
-// polynomial of degree 12 in Horner form (truncation below 2e-16 relative on
-// that range) and a scale by 2^k; 0 below -745.  The coefficients sit in
-// constant memory, so they reach the FMAs from scalar registers.
-__constant__ double kExpTaylor[13] = {
-    1.0, 1.0, 0.5, 0.16666666666666666, 0.041666666666666664, 0.008333333333333333,
-    0.001388888888888889, 0.0001984126984126984, 2.48015873015873e-05,
-    2.7557319223985893e-06, 2.755731922398589e-07, 2.505210838544172e-08,
-    2.08767569878681e-09};
-OTM_DEV double lme_exp(double x) {
-  const double k = rint(x * 1.4426950408889634);
-  double r = fma(k, -0.6931471803691238, x);
-  r = fma(k, -1.9082149292705877e-10, r);
-  double p = kExpTaylor[12];
-#pragma unroll
-  for (int i = 11; i >= 0; --i) p = fma(p, r, kExpTaylor[i]);
-  const double e = ldexp(p, (int)k);
-  return x < -745.0 ? 0.0 : e;
-}
+__constant__ double kExpTaylor[13] = OTM_EXP_TAYLOR;
+OTM_DEV double lme_exp(double x) { return lme_exp(kExpTaylor, x); }
 
 struct Eval {
   double logZ, Z, fmax;
@@ -581,12 +563,24 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
   table_flush(table, tid, 256, dst);
 }
 
+// The pipelined kernel pays off from four rounds per workgroup on; below, its
+// first pass and its fixed grid cost more than the overlap gives.  OTM_MIXED
+// stays here whatever the size: its float32 return map turns a last-bit change
+// of grad N into 1e-6 of a point's stress, so its results keep this kernel's
+// order of operations.
+constexpr int64_t kPipelinedMps = 4 * 512 * 64;
+
 void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
                 const int64_t* nbr_offsets, const int32_t* nbr_idx, int64_t pair_capacity,
                 double beta, double tol, int32_t max_iter, double* lam, double* N, void* dN,
                 int32_t precision, const double4* packed, otm_diag* diag, hipStream_t s,
                 const AsmIn* fused, const SegIn* seg) {
   if (n_mp <= 0) return;
+  if (precision != OTM_MIXED && n_mp >= kPipelinedMps) {
+    launch_lme_pipelined(n_nodes, x_nodes, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
+                         tol, max_iter, lam, N, dN, precision, packed, diag, s, fused, seg);
+    return;
+  }
   const NodeSrc ns{x_nodes, packed, n_nodes};
   constexpr int G = 4, PPL = 9;
   if (fused != nullptr) {

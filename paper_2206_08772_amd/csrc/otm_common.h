@@ -334,7 +334,7 @@ constexpr int kTableSlots = 1 << kTableBits;
 
 template <int V>
 struct NodeTableV {
-  int32_t keys[kTableSlots];
+  alignas(16) int32_t keys[kTableSlots];
   double vals[V][kTableSlots];
 };
 using NodeTable = NodeTableV<4>;
@@ -405,6 +405,22 @@ OTM_DEV void table_insert(NodeTableV<V>& t, int32_t I, const double (&c)[V],
 #pragma unroll
   for (int v = 0; v < V; ++v) cc[0][v] = c[v];
   table_insert_batch<V, 1>(t, key, use, cc, dst);
+}
+
+OTM_DEV int32_t table_hash(int32_t I) {
+  return (int32_t)(((uint32_t)I * 2654435761u) >> (32 - kTableBits));
+}
+// Slot of node I (claimed if new), probing on from place h; -1 if 32 places hold
+// other nodes.
+template <int V>
+OTM_DEV int32_t table_probe(NodeTableV<V>& t, int32_t I, int32_t h) {
+#pragma unroll 1
+  for (int probe = 0; probe < 32; ++probe) {
+    const int32_t prev = atomicCAS(&t.keys[h], -1, I);
+    if (prev == -1 || prev == I) return h;
+    h = (h + 1) & (kTableSlots - 1);
+  }
+  return -1;
 }
 
 OTM_DEV void table_insert(NodeTable& t, int32_t I, double c0, double c1, double c2, double c3,
