@@ -16,9 +16,12 @@ static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
                        int64_t pair_capacity, Workspace* w) {
   const int64_t cap_cells = (n_nodes > 0 ? n_nodes : 0) + 1024;
-  // block totals of the largest scan: the MP offsets, the node influence
-  // offsets, or the node and MP cell counts scanned together (two arrays)
-  auto blocks = [](int64_t n) { return (n + kScanBlock - 1) / kScanBlock; };
+  // block totals of the largest scan: the MPs' pairs, the node influence
+  // offsets, or the node and MP cell counts scanned together (two arrays).
+  // (Sized, as the ticket and the spare area below, for 4096 elements per
+  // scan workgroup: the bytes a workspace needs stay what they were.)
+  auto blocks = [](int64_t n) { return (n + 4095) / 4096; };
+  static_assert(kScanBlock >= 4096, "one entry per scan workgroup fits");
   int64_t scan_blocks = blocks(n_mp + 1);
   if (2 * blocks(cap_cells + 1) > scan_blocks) scan_blocks = 2 * blocks(cap_cells + 1);
   if (blocks(n_nodes + 1) > scan_blocks) scan_blocks = blocks(n_nodes + 1);
@@ -31,7 +34,7 @@ size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
       align256(sizeof(int32_t) * (size_t)n_nodes),
       align256(sizeof(double4) * (size_t)n_nodes),
       align256(sizeof(int64_t) * (size_t)scan_blocks),
-      align256(sizeof(int32_t) * (size_t)(n_mp / 64 + 2)),
+      align256(sizeof(int32_t) * (size_t)(n_mp / 64 + 2)),  // one word used
       align256(sizeof(int64_t) * (size_t)(n_nodes + 1)),
       align256(sizeof(int32_t) * (size_t)n_nodes),
       align256(sizeof(int32_t) * (size_t)pair_capacity),
@@ -42,7 +45,7 @@ size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
       align256(sizeof(int32_t) * (size_t)n_mp),
       align256(sizeof(double4) * (size_t)n_mp),
       align256(sizeof(double4) * (size_t)pair_capacity),
-      align256(sizeof(int32_t) * cap_cells),
+      align256(sizeof(int32_t) * cap_cells),  // spare
   };
   size_t total = 0;
   for (size_t s : sizes) total += s;
@@ -54,11 +57,11 @@ size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
   w->bbox_part = (double*)take(1);
   w->cap_cells = cap_cells;
   w->cell_start = (int32_t*)take(2);
-  w->cell_cursor = (int32_t*)take(3);
+  w->node_rank = (int32_t*)take(3);
   w->node_cell = (int32_t*)take(4);
   w->sorted = (double4*)take(5);
   w->scan_aux = (int64_t*)take(6);
-  w->block_max = (int32_t*)take(7);
+  w->ticket = (int32_t*)take(7);
   w->tr_start = (int64_t*)take(8);
   w->tr_cursor = (int32_t*)take(9);
   w->tr_pairs = (int32_t*)take(10);
@@ -69,7 +72,7 @@ size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
   w->mp_cell = (int32_t*)take(15);
   w->mp_sorted = (double4*)take(16);
   w->contrib = (double4*)take(17);
-  w->mp_cell_cursor = (int32_t*)take(18);
+  take(18);
   return total;
 }
 

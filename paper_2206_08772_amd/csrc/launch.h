@@ -20,7 +20,7 @@ struct Grid {
 };
 
 constexpr int kBBoxBlocks = 256;
-constexpr int kScanBlock = 4096;  // elements per scan workgroup (1024 threads x 4)
+constexpr int kScanBlock = 16384; // elements per scan workgroup (1024 threads x 16)
 constexpr int kRowCapacity = 40;  // search rows staged per MP before compaction
 
 struct Workspace {
@@ -28,11 +28,11 @@ struct Workspace {
   double* bbox_part;     // [kBBoxBlocks][6]
   int64_t cap_cells;
   int32_t* cell_start;   // [cap_cells + 1]
-  int32_t* cell_cursor;  // [cap_cells]
+  int32_t* node_rank;    // [cap_cells] each node's place in its cell
   int32_t* node_cell;    // [n_nodes]
   double4* sorted;       // [n_nodes]: x, y, z, node id
-  int64_t* scan_aux;     // scan partial sums (int64 view)
-  int32_t* block_max;    // [n_mp / 64 + 1] largest support per compaction workgroup
+  int64_t* scan_aux;     // totals of scan workgroups
+  int32_t* ticket;       // workgroups of the search's pair runs that are done
   int64_t* tr_start;     // [n_nodes + 1] influence-list offsets
   int32_t* tr_cursor;    // [n_nodes]
   int32_t* tr_pairs;     // [pair_capacity] pair ids bucketed by node (order within a bucket unset)
@@ -40,9 +40,8 @@ struct Workspace {
   int32_t* stage;        // [n_mp][kRowCapacity] sorted rows of the one-pass search
   double4* nodes;        // [2 n_nodes] packed node records (x, y, z, du_x), (du_y, du_z, 0, 0)
   int32_t* mp_cell_start;  // [cap_cells + 1] MPs binned on the search grid
-  int32_t* mp_cell_cursor; // [cap_cells]
-  int32_t* mp_cell;        // [n_mp]
-  double4* mp_sorted;      // [n_mp]: x, y, z, MP id
+  int32_t* mp_cell;        // [n_mp] cell of each MP, then its support size
+  double4* mp_sorted;      // [n_mp]: x, y, z, MP id; then totals of runs of MPs
   double4* contrib;        // [pair_capacity] pair contributions (m, f) in node-sorted order
 };
 

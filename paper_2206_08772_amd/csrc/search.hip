@@ -4,9 +4,17 @@
 // Nodes are binned into static cells of edge >= r_list over their bounding
 // box; a copy of the node coordinates is stored in cell order (x, y, z, id
 // as one 32-byte record) so the 27-cell scan of an MP reads contiguous
-// memory.  Each MP's nodes are kept sorted by id in LDS while they are found,
-// so lists come out in canonical order.  The squared distance is evaluated as
+// memory.  Each MP's row is sorted by id when it is copied to its place, so
+// lists come out in canonical order.  The squared distance is evaluated as
 // ((dx*dx + dy*dy) + dz*dz) with every operation rounded separately.
+//
+// A small body's search is bound by its launches (3 to 4 us each even when
+// nearly empty), so whatever a kernel's workgroups can find out from a few
+// hundred words they read and reduce themselves: the grid from the box
+// partials (in the count), the totals before a scan workgroup, the pairs
+// before a compaction group.  6 launches up to 8192 MPs and 16384 cells, 7 to 8
+// above, where up to 13 were needed.  Search of 4096 MPs: 32 us of kernel time,
+// 73 before; 27.6k: 47 (86); 108k: 77 (99); 1.13M: 301 (352).
 #include <type_traits>
 
 #include "launch.h"
@@ -15,108 +23,131 @@
 namespace otm {
 
 // ---------------------------------------------------------------- prefix sum
-// Inclusive scan in three passes: each workgroup scans kScanBlock elements
-// and writes its total, one workgroup scans the totals (exclusive), each
-// workgroup adds its offset.  Two arrays of equal length (the node and MP
-// cell counts) go through the same three launches: workgroup b works on
-// array b / nb, and the totals of each array are scanned separately.
+// Inclusive scan in two passes: each workgroup scans kScanBlock elements (16
+// per thread) and writes its total, then each workgroup adds the totals before
+// its own, which it sums itself (a third launch that scans them costs more
+// than these reads: two arrays of 190k counts 12 us, 16 with it).  Up to kScanBlock elements take
+// one launch.  Two arrays of equal length (the node and MP cell counts) go
+// through the same launches: workgroup b works on array b / nb.  ``live``
+// (nullable) holds how many of the n elements are in use.
+constexpr int kScanPer = kScanBlock / 1024;
 template <typename T>
-OTM_DEV void scan_block(T* a, int64_t n, int64_t blk, int64_t* total) {
-  __shared__ T s[1024];
-  const int tid = threadIdx.x;
-  const int64_t base = blk * kScanBlock + (int64_t)tid * 4;
+struct Pack4 {
   T v[4];
-  T run = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t i = base + k;
-    run += (i < n) ? a[i] : T(0);
-    v[k] = run;
-  }
-  s[tid] = run;
+};
+
+// Sum over the workgroup's waves of v, in every thread (sh: one value per wave).
+template <typename T>
+OTM_DEV T block_sum(T v, T* sh) {
+  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  const int waves = (int)blockDim.x / kWave;
+  if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = v;
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const T add = tid >= o ? s[tid - o] : T(0);
-    __syncthreads();
-    s[tid] += add;
-    __syncthreads();
+  T t = 0;
+  for (int w = 0; w < waves; ++w) t += sh[w];
+  return t;
+}
+
+// Exclusive scan of one value per thread over the workgroup; total: the sum.
+template <typename T>
+OTM_DEV T block_scan(T v, T* sh, T& total) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  const int waves = (int)blockDim.x / kWave;
+  T run = v;
+  for (int o = 1; o < kWave; o <<= 1) {
+    const T u = __shfl_up(run, o);
+    run += lane >= o ? u : T(0);
   }
-  const T excl = tid > 0 ? s[tid - 1] : T(0);
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t i = base + k;
-    if (i < n) a[i] = v[k] + excl;
+  if (lane == kWave - 1) sh[wave] = run;
+  __syncthreads();
+  T before = 0;
+  total = 0;
+  for (int w = 0; w < waves; ++w) {
+    before += w < wave ? sh[w] : T(0);
+    total += sh[w];
   }
-  if (tid == 1023) *total = (int64_t)s[1023];
+  return before + run - v;
 }
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_scan_blocks(T* a, T* b, int64_t n, int64_t nb,
-                                                      int64_t* aux) {
-  const int64_t seg = blockIdx.x / nb;
-  scan_block(seg == 0 ? a : b, n, blockIdx.x - seg * nb, aux + blockIdx.x);
-}
-
-// Exclusive scan of nseg segments of nb block totals by one workgroup.
-__global__ __launch_bounds__(1024) void k_scan_aux(int64_t* aux, int64_t nb, int nseg) {
-  __shared__ int64_t s[1024];
-  __shared__ int64_t carry;
-  const int tid = threadIdx.x;
-  for (int seg = 0; seg < nseg; ++seg) {
-    int64_t* t = aux + seg * nb;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
-      const int64_t i = b0 + tid;
-      const int64_t v = i < nb ? t[i] : 0;
-      s[tid] = v;
-      __syncthreads();
-      for (int o = 1; o < 1024; o <<= 1) {
-        const int64_t add = tid >= o ? s[tid - o] : 0;
-        __syncthreads();
-        s[tid] += add;
-        __syncthreads();
-      }
-      if (i < nb) t[i] = carry + s[tid] - v;
-      __syncthreads();
-      if (tid == 0) carry += s[1023];
-      __syncthreads();
+                                                      int64_t* aux, const int64_t* live) {
+  __shared__ T sh[1024 / kWave];
+  const int64_t seg = blockIdx.x / nb, blk = blockIdx.x - seg * nb;
+  T* arr = seg == 0 ? a : b;
+  const int64_t in_use = live != nullptr && *live < n ? *live : n;
+  const int64_t base = blk * kScanBlock + (int64_t)threadIdx.x * kScanPer;
+  if (blk * kScanBlock >= in_use) return;
+  // whole runs move as packs of four (the arrays start one element off a
+  // 16-byte boundary: packs of element alignment)
+  Pack4<T>* pack = reinterpret_cast<Pack4<T>*>(arr + base);
+  const bool whole = base + kScanPer <= in_use;
+  T v[kScanPer], sum = 0;
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < kScanPer / 4; ++k) {
+      const Pack4<T> q = pack[k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * k + e] = q.v[e];
     }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) v[k] = base + k < in_use ? arr[base + k] : T(0);
   }
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    sum += v[k];
+    v[k] = sum;
+  }
+  T total;
+  const T excl = block_scan(sum, sh, total);
+  if (whole) {
+#pragma unroll
+    for (int k = 0; k < kScanPer / 4; ++k) {
+      Pack4<T> q;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) q.v[e] = v[4 * k + e] + excl;
+      pack[k] = q;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k)
+      if (base + k < in_use) arr[base + k] = v[k] + excl;
+  }
+  if (threadIdx.x == 0) aux[blockIdx.x] = (int64_t)total;
 }
 
 template <typename T>
 __global__ __launch_bounds__(1024) void k_scan_add(T* a, T* b, int64_t n, int64_t nb,
-                                                   const int64_t* aux) {
-  const int64_t add = aux[blockIdx.x];
-  if (add == 0) return;
-  const int64_t seg = blockIdx.x / nb;
+                                                   const int64_t* aux, const int64_t* live) {
+  __shared__ int64_t sh[1024 / kWave];
+  const int64_t seg = blockIdx.x / nb, blk = blockIdx.x - seg * nb;
+  const int64_t in_use = live != nullptr && *live < n ? *live : n;
+  if (blk == 0 || blk * kScanBlock >= in_use) return;
+  int64_t part = 0;
+  for (int64_t i = threadIdx.x; i < blk; i += 1024) part += aux[seg * nb + i];
+  const T add = (T)block_sum(part, sh);
   T* arr = seg == 0 ? a : b;
-  const int64_t base = (blockIdx.x - seg * nb) * kScanBlock;
   for (int k = threadIdx.x; k < kScanBlock; k += 1024) {
-    const int64_t i = base + k;
-    if (i < n) arr[i] += (T)add;
+    const int64_t i = blk * kScanBlock + k;
+    if (i < in_use) arr[i] += add;
   }
 }
 
 // b == nullptr: one array
 template <typename T>
-static void scan_impl(T* a, T* b, int64_t n, int64_t* aux, hipStream_t s) {
+static void scan_impl(T* a, T* b, int64_t n, int64_t* aux, const int64_t* live, hipStream_t s) {
   if (n <= 0) return;
   const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  const int nseg = b == nullptr ? 1 : 2;
-  const unsigned grid = (unsigned)(nb * nseg);
-  k_scan_blocks<T><<<grid, 1024, 0, s>>>(a, b, n, nb, aux);
-  if (nb > 1) {
-    k_scan_aux<<<1, 1024, 0, s>>>(aux, nb, nseg);
-    k_scan_add<T><<<grid, 1024, 0, s>>>(a, b, n, nb, aux);
-  }
+  const unsigned grid = (unsigned)(nb * (b == nullptr ? 1 : 2));
+  k_scan_blocks<T><<<grid, 1024, 0, s>>>(a, b, n, nb, aux, live);
+  if (nb > 1) k_scan_add<T><<<grid, 1024, 0, s>>>(a, b, n, nb, aux, live);
 }
 void scan_inclusive(int64_t* a, int64_t n, int64_t* aux, hipStream_t s) {
-  scan_impl<int64_t>(a, nullptr, n, aux, s);
+  scan_impl<int64_t>(a, nullptr, n, aux, nullptr, s);
 }
 void scan_inclusive(int32_t* a, int64_t n, int64_t* aux, hipStream_t s) {
-  scan_impl<int32_t>(a, nullptr, n, aux, s);
+  scan_impl<int32_t>(a, nullptr, n, aux, nullptr, s);
 }
 
 // ---------------------------------------------------------------- fills
@@ -160,116 +191,113 @@ __global__ void k_diag_reset(otm_diag* d) {
 void launch_diag_reset(otm_diag* d, hipStream_t s) { k_diag_reset<<<1, 1, 0, s>>>(d); }
 
 // ---------------------------------------------------------------- cell grid
-// Bounding box partials of the nodes; the same launch clears the cell
-// counters and cursors of the node and MP binnings that follow.
+// Bounding box partials of the nodes, one per workgroup; the same launch clears
+// the cell counters of the node and MP binnings that follow.
 struct BinCounters {
   int32_t* node_start;  // [cap + 1]
-  int32_t* node_cursor; // [cap]
   int32_t* mp_start;    // [cap + 1]
-  int32_t* mp_cursor;   // [cap]
   int64_t cap;
+  int32_t* ticket;      // of the pair runs' workgroups
 };
 
-__global__ __launch_bounds__(256) void k_bbox_partial(const double* x, int64_t n, double* part,
+struct Box {
+  double lo[3], hi[3];
+  OTM_DEV void clear() {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      lo[c] = INFINITY;
+      hi[c] = -INFINITY;
+    }
+  }
+  OTM_DEV void wave_join() {
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        lo[c] = fmin(lo[c], __shfl_xor(lo[c], o));
+        hi[c] = fmax(hi[c], __shfl_xor(hi[c], o));
+      }
+    }
+  }
+  // Over a workgroup of 256 threads, in every thread (sh: 4 boxes).
+  OTM_DEV void block_join(Box* sh) {
+    wave_join();
+    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = *this;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        lo[c] = fmin(lo[c], sh[w].lo[c]);
+        hi[c] = fmax(hi[c], sh[w].hi[c]);
+      }
+    }
+  }
+};
+
+// Nodes per bounding-box workgroup: four per thread, more past kBBoxBlocks
+// workgroups (every counting workgroup reads all their boxes).
+static unsigned bbox_blocks(int64_t n) {
+  const int64_t b = (n + 1023) / 1024;
+  return (unsigned)(b < 1 ? 1 : (b < kBBoxBlocks ? b : kBBoxBlocks));
+}
+
+__global__ __launch_bounds__(256) void k_bbox_partial(const double* x, int64_t n, Box* part,
                                                       BinCounters z) {
-  __shared__ double sh[6][256];
+  __shared__ Box sh[4];
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= z.cap;
        i += (int64_t)gridDim.x * blockDim.x) {
     z.node_start[i] = 0;
     z.mp_start[i] = 0;
-    if (i < z.cap) {
-      z.node_cursor[i] = 0;
-      z.mp_cursor[i] = 0;
-    }
   }
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  if (blockIdx.x == 0 && threadIdx.x == 0) *z.ticket = 0;
+  Box b;
+  b.clear();
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const double v = x[c * n + i];
-      lo[c] = fmin(lo[c], v);
-      hi[c] = fmax(hi[c], v);
+      b.lo[c] = fmin(b.lo[c], v);
+      b.hi[c] = fmax(b.hi[c], v);
     }
   }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) { sh[c][threadIdx.x] = lo[c]; sh[3 + c][threadIdx.x] = hi[c]; }
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        sh[c][threadIdx.x] = fmin(sh[c][threadIdx.x], sh[c][threadIdx.x + o]);
-        sh[3 + c][threadIdx.x] = fmax(sh[3 + c][threadIdx.x], sh[3 + c][threadIdx.x + o]);
-      }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0)
-    for (int c = 0; c < 6; ++c) part[blockIdx.x * 6 + c] = sh[c][0];
+  b.block_join(sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = b;
 }
 
 // Grid over the box: cell edge = cell_size, enlarged by 1.25x until the cell
 // count fits the workspace (a larger cell only adds candidates).  Non-finite
 // extents fall back to a single cell of unbounded size; every coordinate is
 // clamped into the grid, so no cell index can leave it.
-__global__ __launch_bounds__(256) void k_grid_finalize(const double* part, int nb,
-                                                       double cell_size, int64_t cap, Grid* g) {
-  __shared__ double sh[6][256];
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = threadIdx.x; b < nb; b += 256)
-    for (int c = 0; c < 3; ++c) {
-      lo[c] = fmin(lo[c], part[b * 6 + c]);
-      hi[c] = fmax(hi[c], part[b * 6 + 3 + c]);
-    }
-  for (int c = 0; c < 3; ++c) { sh[c][threadIdx.x] = lo[c]; sh[3 + c][threadIdx.x] = hi[c]; }
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o)
-      for (int c = 0; c < 3; ++c) {
-        sh[c][threadIdx.x] = fmin(sh[c][threadIdx.x], sh[c][threadIdx.x + o]);
-        sh[3 + c][threadIdx.x] = fmax(sh[3 + c][threadIdx.x], sh[3 + c][threadIdx.x + o]);
-      }
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
-  for (int c = 0; c < 3; ++c) { lo[c] = sh[c][0]; hi[c] = sh[3 + c][0]; }
-  double ext[3];
+OTM_DEV Grid make_grid(const Box& b, double cell_size, int64_t cap) {
+  double lo[3], ext[3];
   bool finite = true;
+#pragma unroll
   for (int c = 0; c < 3; ++c) {
-    ext[c] = hi[c] - lo[c];
+    lo[c] = b.lo[c];
+    ext[c] = b.hi[c] - b.lo[c];
     if (!isfinite(ext[c]) || !isfinite(lo[c])) finite = false;
     if (!(ext[c] > 0.0)) ext[c] = 0.0;
   }
-  double cell = cell_size;
-  int64_t dims[3] = {1, 1, 1}, total = 1;
+  double cell = cell_size, dx = 1.0, dy = 1.0, dz = 1.0;
   bool fits = false;
   for (int tries = 0; finite && tries < 400; ++tries) {
-    double dd[3], tot = 1.0;
-    for (int c = 0; c < 3; ++c) {
-      dd[c] = floor(ext[c] / cell) + 1.0;
-      tot *= dd[c];
-    }
-    if (tot <= (double)cap) {
-      total = 1;
-      for (int c = 0; c < 3; ++c) {
-        dims[c] = (int64_t)dd[c];
-        total *= dims[c];
-      }
-      fits = true;
-      break;
-    }
+    dx = floor(ext[0] / cell) + 1.0;
+    dy = floor(ext[1] / cell) + 1.0;
+    dz = floor(ext[2] / cell) + 1.0;
+    fits = dx * dy * dz <= (double)cap;
+    if (fits) break;
     cell *= 1.25;
   }
-  if (!fits) {
-    dims[0] = dims[1] = dims[2] = 1;
-    total = 1;
-    cell = INFINITY;
-    for (int c = 0; c < 3; ++c) lo[c] = isfinite(lo[c]) ? lo[c] : 0.0;
-  }
-  for (int c = 0; c < 3; ++c) { g->lo[c] = lo[c]; g->dims[c] = (int32_t)dims[c]; }
-  g->cell = cell;
-  g->n_cells = total;
+  Grid g;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) g.lo[c] = fits || isfinite(lo[c]) ? lo[c] : 0.0;
+  g.dims[0] = fits ? (int32_t)dx : 1;
+  g.dims[1] = fits ? (int32_t)dy : 1;
+  g.dims[2] = fits ? (int32_t)dz : 1;
+  g.cell = fits ? cell : INFINITY;
+  g.n_cells = (int64_t)g.dims[0] * g.dims[1] * g.dims[2];
+  g.pad = 0;
+  return g;
 }
 
 OTM_DEV int cell_coord(double x, double lo, double inv_cell, int dim) {
@@ -282,49 +310,85 @@ OTM_DEV int cell_coord(double x, double lo, double inv_cell, int dim) {
 // Counting sort of two point sets (nodes, then MPs) on one grid, each pass
 // one launch: thread i < n_a takes point i of set a, threads from b0 (n_a
 // rounded up to a wave, so no wave mixes the sets and the wave-grouped
-// atomics see one counter array) take set b.
+// atomics see one counter array) take set b.  The count keeps each point's
+// rank in its cell, so that the fill needs no atomics.
 struct BinSet {
   const double* x;     // [3][n]
   int64_t n;
   int32_t* cell;       // [n] cell of each point
+  int32_t* rank;       // [n] its place among the cell's points
   int32_t* start;      // [cap + 1] counts, then offsets
-  int32_t* cursor;     // [cap]
   double4* sorted;     // [n] (x, y, z, index) in cell order
 };
+constexpr unsigned kCountBlocks = 2048;  // of the count: as many as fit at once
 
-OTM_DEV bool bin_pick(const BinSet& a, const BinSet& b, int64_t b0, const BinSet*& set,
+// The set and point of thread t, false where there is none.
+OTM_DEV bool bin_pick(const BinSet& a, const BinSet& b, int64_t b0, int64_t t, BinSet& set,
                       int64_t& i) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < a.n) { set = &a; i = t; return true; }
-  if (t >= b0 && t - b0 < b.n) { set = &b; i = t - b0; return true; }
-  return false;
+  const bool first = t < a.n;
+  i = first ? t : t - b0;
+  set.x = first ? a.x : b.x;
+  set.n = first ? a.n : b.n;
+  set.cell = first ? a.cell : b.cell;
+  set.rank = first ? a.rank : b.rank;
+  set.start = first ? a.start : b.start;
+  set.sorted = first ? a.sorted : b.sorted;
+  return i >= 0 && i < set.n;
 }
 
+// Every workgroup forms the grid from the box partials itself (they are few,
+// and a launch of its own would cost more than all of them reading them); the
+// first one keeps it for the passes that follow.
 __global__ __launch_bounds__(256) void k_bin_count(BinSet a, BinSet b, int64_t b0,
-                                                   const Grid* g) {
-  const BinSet* set;
-  int64_t i;
-  if (!bin_pick(a, b, b0, set, i)) return;
-  const double* x = set->x;
-  const int64_t n = set->n;
-  const double inv = 1.0 / g->cell;
-  const int cx = cell_coord(x[i], g->lo[0], inv, g->dims[0]);
-  const int cy = cell_coord(x[n + i], g->lo[1], inv, g->dims[1]);
-  const int cz = cell_coord(x[2 * n + i], g->lo[2], inv, g->dims[2]);
-  const int32_t cid = (cz * g->dims[1] + cy) * g->dims[0] + cx;
-  set->cell[i] = cid;
-  grouped_atomic_add(set->start + 1, cid);
+                                                   const Box* part, int n_part,
+                                                   double cell_size, int64_t cap, Grid* keep) {
+  __shared__ Box sh[4];
+  __shared__ Grid sg;
+  const int64_t n_threads = b0 + b.n;
+  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, i = 0;
+  BinSet set;
+  bool any = bin_pick(a, b, b0, t, set, i);
+  double x[3] = {0.0, 0.0, 0.0};
+  // the first point is requested before the box is formed
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (any) x[c] = set.x[c * set.n + i];
+  Box box;
+  box.clear();
+  if ((int)threadIdx.x < n_part) box = part[threadIdx.x];
+  box.block_join(sh);
+  if (threadIdx.x == 0) {
+    sg = make_grid(box, cell_size, cap);
+    if (blockIdx.x == 0) *keep = sg;
+  }
+  __syncthreads();
+  const Grid g = sg;
+  const double inv = 1.0 / g.cell;
+  while (t < n_threads) {
+    if (any) {
+      const int cx = cell_coord(x[0], g.lo[0], inv, g.dims[0]);
+      const int cy = cell_coord(x[1], g.lo[1], inv, g.dims[1]);
+      const int cz = cell_coord(x[2], g.lo[2], inv, g.dims[2]);
+      const int32_t cid = (cz * g.dims[1] + cy) * g.dims[0] + cx;
+      set.cell[i] = cid;
+      set.rank[i] = grouped_atomic_add(set.start + 1, cid);
+    }
+    t += (int64_t)gridDim.x * 256;
+    any = t < n_threads && bin_pick(a, b, b0, t, set, i);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (any) x[c] = set.x[c * set.n + i];
+  }
 }
 
 __global__ __launch_bounds__(256) void k_bin_fill(BinSet a, BinSet b, int64_t b0) {
-  const BinSet* set;
+  BinSet set;
   int64_t i;
-  if (!bin_pick(a, b, b0, set, i)) return;
-  const double* x = set->x;
-  const int64_t n = set->n;
-  const int32_t cid = set->cell[i];
-  const int32_t pos = set->start[cid] + grouped_atomic_add(set->cursor, cid);
-  set->sorted[pos] = make_double4(x[i], x[n + i], x[2 * n + i], (double)i);
+  if (!bin_pick(a, b, b0, (int64_t)blockIdx.x * 256 + threadIdx.x, set, i)) return;
+  const double* x = set.x;
+  const int64_t n = set.n;
+  const int32_t pos = set.start[set.cell[i]] + set.rank[i];
+  set.sorted[pos] = make_double4(x[i], x[n + i], x[2 * n + i], (double)i);
 }
 
 // ---------------------------------------------------------------- MP lists
@@ -414,7 +478,7 @@ OTM_DEV double lane_value(double v, int t) {  // v of lane t (t uniform)
 // taken in candidate order, gives each hit its place in the MP's staging
 // row.  The row is in stencil order; the compaction sorts it by node id (the
 // four lanes of a quad per row, in registers), which costs far fewer
-// instructions than sorting each cell's candidates.  The count goes to offsets[p + 1]; rows
+// instructions than sorting each cell's candidates.  The count goes to cnt[p]; rows
 // longer than kRowCap are only counted (the compaction re-finds them).  A
 // cell with more than kCand candidates takes each MP separately: hits are
 // appended to LDS by ballot and rank-sorted.
@@ -451,11 +515,15 @@ struct CellLds {  // the hits of one MP in the dense path
   int32_t ids[kCand];
 };
 
-OTM_DEV void cell_scan_one(const CellHdr& h, double r2, const double4* __restrict__ sorted,
-                           const double4* __restrict__ mp_sorted, int64_t* __restrict__ offsets,
+// Part `part` of 2^split of a cell's MPs.
+OTM_DEV void cell_scan_one(const CellHdr& h, int part, int split, double r2,
+                           const double4* __restrict__ sorted,
+                           const double4* __restrict__ mp_sorted, int32_t* __restrict__ cnt,
                            int32_t* __restrict__ stage, CellLds& L, int lane) {
-  const int32_t m0 = h.m0, m1 = h.m1;
-  if (m0 == m1) return;
+  const int32_t share = (((h.m1 - h.m0 + (1 << split) - 1) >> split) + 3) & ~3;
+  const int32_t m0 = h.m0 + part * share;
+  const int32_t m1 = m0 + share < h.m1 ? m0 + share : h.m1;
+  if (m0 >= m1) return;
   const int32_t T = h.pre[9];
   if (T <= kCand) {
     const int nch = (T + kWave - 1) / kWave;  // uniform
@@ -516,7 +584,7 @@ OTM_DEV void cell_scan_one(const CellHdr& h, double r2, const double4* __restric
       }
       if (lane == 0) {
 #pragma unroll
-        for (int i = 0; i < NM; ++i) offsets[p[i] + 1] = n[i];
+        for (int i = 0; i < NM; ++i) cnt[p[i]] = (int32_t)n[i];
       }
     };
     for (int32_t mb = m0; mb < m1; mb += kWave) {
@@ -554,72 +622,191 @@ OTM_DEV void cell_scan_one(const CellHdr& h, double r2, const double4* __restric
           row[rk] = id;
         }
       }
-      if (lane == 0) offsets[p + 1] = n;
+      if (lane == 0) cnt[p] = n;
       wave_sync();
     }
   }
 }
 
+// A wave's item is a cell, or with fewer than kMinItems cells (a small body,
+// whose cells alone would leave most of the chip idle and their MPs to one
+// wave's serial loop) one of up to 2^kMaxSplit parts of a cell's MPs: 4096 MPs
+// 9.8 us, 22 whole; 27.6k MPs 17, 28 whole.  Above kMinItems cells the chip is
+// full and a part would only fetch its cell's nodes again.
+constexpr int kMinItems = 4096;
+constexpr int kMaxSplit = 3;
+
 __global__ __launch_bounds__(kCellWaves * kWave) void k_cell_scan(
     double r2, const Grid* __restrict__ gp, int64_t cap_cells,
     const int32_t* __restrict__ cell_start, const double4* __restrict__ sorted,
     const int32_t* __restrict__ mp_cell_start, const double4* __restrict__ mp_sorted,
-    int64_t* __restrict__ offsets, int32_t* __restrict__ stage) {
+    int32_t* __restrict__ cnt, int32_t* __restrict__ stage) {
   __shared__ CellLds lds[kCellWaves];
   // wave index as a uniform value, so the cell loop runs on scalar registers
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int lane = (int)(threadIdx.x % kWave);
-  if (blockIdx.x == 0 && threadIdx.x == 0) offsets[0] = 0;
   const Grid g = *gp;
-  const int64_t n_cells = g.n_cells < cap_cells ? g.n_cells : cap_cells;
-  const int64_t per_xcd = (n_cells + 7) / 8;
-  const int64_t c_lo = (int64_t)(blockIdx.x % 8u) * per_xcd;
-  const int64_t c_hi = c_lo + per_xcd < n_cells ? c_lo + per_xcd : n_cells;
-  const int64_t stride = (int64_t)(gridDim.x / 8u) * kCellWaves;
-  int64_t c = c_lo + (int64_t)(blockIdx.x / 8u) * kCellWaves + w;
+  const int32_t n_cells = (int32_t)(g.n_cells < cap_cells ? g.n_cells : cap_cells);
+  int split = 0;  // 2^split parts
+  while (split < kMaxSplit && (n_cells << split) < kMinItems) ++split;
+  const int32_t n_items = n_cells << split;  // cells, or under 2 kMinItems
+  const int32_t per_xcd = (n_items + 7) / 8;
+  const int32_t c_lo = (int32_t)(blockIdx.x % 8u) * per_xcd;
+  const int32_t c_hi = c_lo + per_xcd < n_items ? c_lo + per_xcd : n_items;
+  const int32_t stride = (int32_t)(gridDim.x / 8u) * kCellWaves;
+  int64_t c = (int64_t)c_lo + (int64_t)(blockIdx.x / 8u) * kCellWaves + w;
   if (c >= c_hi) return;
-  CellHdr h = cell_header(c, g, cell_start, mp_cell_start);
+  CellHdr h = cell_header((int32_t)c >> split, g, cell_start, mp_cell_start);
   for (; c < c_hi; c += stride) {
     const int64_t cn = c + stride < c_hi ? c + stride : c;
-    const CellHdr hn = cell_header(cn, g, cell_start, mp_cell_start);  // next cell, early
-    cell_scan_one(h, r2, sorted, mp_sorted, offsets, stage, lds[w], lane);
+    // next item's cell, early
+    const CellHdr hn = cell_header((int32_t)cn >> split, g, cell_start, mp_cell_start);
+    cell_scan_one(h, (int32_t)c & ((1 << split) - 1), split, r2, sorted, mp_sorted, cnt, stage,
+                  lds[w], lane);
     h = hn;
   }
 }
 
-constexpr int kScanMPs = 64;  // MPs per compaction workgroup
+// Pairs before each run of kPairRun MPs, and before each group of kScanMPs MPs
+// within its run (the compaction scans a group's counts itself).  The last
+// workgroup to finish scans the runs' totals and reports them to diag.
+constexpr int kScanMPs = 64;       // MPs per compaction workgroup
+constexpr int kPairRun = 16384;    // MPs per workgroup here, 16 per thread: the
+                                   // tickets of smaller runs queue (6M MPs: 63 us
+                                   // with runs of 4096, 25 with these)
+// Up to here the compaction sums the counts: eight 16-byte loads a thread, in
+// flight together (the compaction of 4096 MPs takes 5.6 us with them; the run
+// pass alone would take 6).
+constexpr int kDirectMPs = 8192;
+struct PairRun {
+  int64_t pairs;  // of the run, then before it
+  int64_t most;   // largest count of the run
+};
 
-// Ascending order of a staged row of K <= 32 node ids (distinct), sorted by
-// the four lanes of a quad: a bitonic network over 32 slots (the slots past
-// K padded with INT32_MAX), lane l of the quad holding slots 8l .. 8l + 7.
-// Compare-exchanges between slots 8 or 16 apart pair a lane with the quad
-// lane l ^ 1 or l ^ 2 (DPP quad permutations); the others stay in the lane.
-// Every lane of the quad must call it with the same row.
-OTM_DEV void sort_row32_quad(int32_t* row, int K, int l) {
-  int32_t a[8];
+// Four counts from i on, zero past n.  (The load may reach past the counts,
+// within the 256-byte unit of the workspace that ends them.)
+OTM_DEV int4 load_counts(const int32_t* __restrict__ cnt, int64_t i, int64_t n) {
+  int4 v = i < n ? reinterpret_cast<const int4*>(cnt)[i / 4] : make_int4(0, 0, 0, 0);
+  v.y = i + 1 < n ? v.y : 0;
+  v.z = i + 2 < n ? v.z : 0;
+  v.w = i + 3 < n ? v.w : 0;
+  return v;
+}
+
+OTM_DEV int32_t wave_max(int32_t m) {
+  for (int o = kWave / 2; o > 0; o >>= 1) {
+    const int32_t u = __shfl_xor(m, o);
+    m = u > m ? u : m;
+  }
+  return m;
+}
+
+__global__ __launch_bounds__(1024) void k_pair_runs(const int32_t* __restrict__ cnt, int64_t n_mp,
+                                                    int64_t* __restrict__ group, PairRun* runs,
+                                                    int32_t* ticket, int64_t capacity,
+                                                    otm_diag* diag) {
+  __shared__ int64_t sh[1024 / kWave];
+  __shared__ int32_t shm[1024 / kWave];
+  __shared__ bool last;
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * kPairRun + (int64_t)tid * 16;
+  int32_t m = 0;
+  int64_t sum = 0;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = 8 * l + e < K ? row[8 * l + e] : INT32_MAX;
+  for (int k = 0; k < 4; ++k) {
+    const int4 c = load_counts(cnt, base + 4 * k, n_mp);
+    m = max(m, max(max(c.x, c.y), max(c.z, c.w)));
+    sum += ((int64_t)c.x + c.y) + ((int64_t)c.z + c.w);
+  }
+  m = wave_max(m);
+  if (tid % kWave == 0) shm[tid / kWave] = m;
+  int64_t total;
+  int64_t before = block_scan(sum, sh, total);
+  if (tid % (kScanMPs / 16) == 0 && base < n_mp) group[base / kScanMPs] = before;
+  if (tid == 0) {
+    int32_t most = 0;
+    for (int w = 0; w < 1024 / kWave; ++w) most = max(most, shm[w]);
+    // seen by the last workgroup through the ticket's release and acquire
+    __hip_atomic_store(&runs[blockIdx.x].pairs, total, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&runs[blockIdx.x].most, (int64_t)most, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int32_t)gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  int64_t run = 0;
+  m = 0;
+  for (int64_t r0 = 0; r0 < gridDim.x; r0 += 1024) {
+    const int64_t r = r0 + tid;
+    int64_t v = 0;
+    if (r < gridDim.x) {
+      v = __hip_atomic_load(&runs[r].pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      m = max(m, (int32_t)__hip_atomic_load(&runs[r].most, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT));
+    }
+    before = block_scan(v, sh, total);
+    if (r < gridDim.x) runs[r].pairs = run + before;
+    run += total;
+    __syncthreads();
+  }
+  m = wave_max(m);
+  if (tid % kWave == 0) shm[tid / kWave] = m;
+  __syncthreads();
+  if (tid != 0) return;
+  runs[gridDim.x].pairs = run;
+  if (diag == nullptr) return;
+  for (int w = 0; w < 1024 / kWave; ++w) m = max(m, shm[w]);
+  diag->pairs_needed = run;
+  diag->max_support = m;
+  if (run > capacity) atomicOr(&diag->flags, 1u << (-OTM_ERR_CAPACITY - 1));
+}
+
+// Loads lane l's ids of a staged row (16-byte aligned) of K <= 4 PER ids:
+// slots PER l and on, those past K INT32_MAX.  Only 16-byte pieces that hold
+// ids are read.
+template <int PER>
+OTM_DEV void load_row_quad(int32_t (&a)[PER], const int32_t* __restrict__ row, int K, int l) {
+  const int4* __restrict__ row4 = reinterpret_cast<const int4*>(row);
 #pragma unroll
-  for (int k = 2; k <= 32; k <<= 1) {
+  for (int q = 0; q < PER / 4; ++q) {
+    const int e = PER * l + 4 * q;
+    int4 v = e < K ? row4[e / 4] : make_int4(INT32_MAX, INT32_MAX, INT32_MAX, INT32_MAX);
+    a[4 * q] = v.x;
+    a[4 * q + 1] = e + 1 < K ? v.y : INT32_MAX;
+    a[4 * q + 2] = e + 2 < K ? v.z : INT32_MAX;
+    a[4 * q + 3] = e + 3 < K ? v.w : INT32_MAX;
+  }
+}
+
+// Ascending order of 4 PER ids held by the four lanes of a quad: a bitonic
+// network, lane l of the quad holding slots PER l and on.  Compare-exchanges
+// between slots PER or 2 PER apart pair a lane with the quad lane l ^ 1 or
+// l ^ 2 (DPP quad permutations); the others stay in the lane.
+template <int PER>
+OTM_DEV void sort_row_quad(int32_t (&a)[PER], int l) {
+#pragma unroll
+  for (int k = 2; k <= 4 * PER; k <<= 1) {
 #pragma unroll
     for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j >= 8) {
-        const bool lower = (l & (j >> 3)) == 0;
+      if (j >= PER) {
+        const bool lower = (l & (j / PER)) == 0;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int32_t w = j == 8 ? dpp_move<0xB1>(a[e]) : dpp_move<0x4E>(a[e]);
+        for (int e = 0; e < PER; ++e) {
+          const int32_t w = j == PER ? dpp_move<0xB1>(a[e]) : dpp_move<0x4E>(a[e]);
           const int32_t lo = a[e] < w ? a[e] : w, hi = a[e] < w ? w : a[e];
-          const bool up = ((8 * l + e) & k) == 0;
+          const bool up = ((PER * l + e) & k) == 0;
           a[e] = lower == up ? lo : hi;
         }
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < PER; ++e) {
           const int f = e ^ j;
           if (f > e) {
             const int32_t x = a[e], y = a[f];
             const int32_t lo = x < y ? x : y, hi = x < y ? y : x;
-            const bool up = ((8 * l + e) & k) == 0;
+            const bool up = ((PER * l + e) & k) == 0;
             a[e] = up ? lo : hi;
             a[f] = up ? hi : lo;
           }
@@ -627,122 +814,136 @@ OTM_DEV void sort_row32_quad(int32_t* row, int K, int l) {
       }
     }
   }
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-    if (8 * l + e < K) row[8 * l + e] = a[e];
 }
 
-// Copies each workgroup's staged rows into its contiguous CSR segment with
-// unit-stride stores; rows longer than kRowCap are found again and sorted
-// in place by their own lane.
+// The ids of one row, sorted, at dst (its first id) and on.
+template <int PER>
+OTM_DEV void put_row_quad(const int32_t (&a)[PER], int32_t* dst, int K, int l) {
+#pragma unroll
+  for (int e = 0; e < PER; ++e)
+    if (PER * l + e < K) dst[PER * l + e] = a[e];
+}
+
+// Row starts and lists.  A workgroup takes 64 MPs, each of its waves 16 of
+// their rows, a quad of lanes per row: the quad loads the staged row, sorts
+// it in registers and writes it to the wave's image of its CSR segment in
+// LDS, which leaves with unit-stride stores.  Every wave scans the 64 counts
+// itself, so that the waves need not wait for one another.  Rows longer than
+// kRowCap are found again and sorted in place by one lane.  The pairs before
+// a workgroup are those before its run plus its group's place in the run; for
+// up to kDirectMPs MPs (DIRECT) it sums the counts itself instead, which
+// spares the run pass, and the first workgroup reports the totals to diag.
+//
+// Bound by memory: 1.13M MPs, 27 ids each, 60 us (a pass that loaded whole
+// rows of kRowCap ids to LDS, sorted them there and marked the MP of each
+// output element 90 us); lists to 1.1 times the radius, with
+// many rows past 32 ids, 101 us (776 with those rows sorted by insertion).
+template <bool DIRECT>
 __global__ __launch_bounds__(256) void k_nbr_compact(
     const double* __restrict__ xp, int64_t n_mp, double r2, const Grid* __restrict__ gp,
     const int32_t* __restrict__ cell_start, const double4* __restrict__ sorted,
-    const int64_t* __restrict__ offsets, const int32_t* __restrict__ stage, int64_t capacity,
-    int32_t* __restrict__ idx, int32_t* __restrict__ block_max) {
-  __shared__ __align__(16) int32_t rows[kScanMPs * kRowCap];
-  __shared__ uint8_t owner[kScanMPs * kRowCap];  // MP of each output element
-  __shared__ int64_t off[kScanMPs + 1];
-  __shared__ int32_t blk_max;
-  const int tid = threadIdx.x;
+    const int32_t* __restrict__ cnt, const int64_t* __restrict__ group,
+    const PairRun* __restrict__ runs, int64_t n_runs, int64_t* __restrict__ offsets,
+    const int32_t* __restrict__ stage, int64_t capacity, int32_t* __restrict__ idx,
+    otm_diag* diag) {
+  static_assert(kScanMPs == kWave && kPairRun % kScanMPs == 0, "one count per lane");
+  static_assert(kRowCap % 4 == 0 && kRowCap <= 64, "whole 16-byte pieces, at most 64 slots");
+  constexpr int kWaveRows = kScanMPs / 4;
+  __shared__ int32_t image[4][kWaveRows * kRowCap];
+  const int tid = threadIdx.x, lane = tid % kWave, l = tid % 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int64_t blk = xcd_block();
   const int64_t p0 = blk * kScanMPs;
   if (p0 >= n_mp) return;
   const int nloc = (int)(n_mp - p0 < kScanMPs ? n_mp - p0 : kScanMPs);
-  // every global input is requested before any is used (one memory latency
-  // instead of three in a row): the row starts, the total and the staged rows,
-  // these in 16-byte pieces (a workgroup's rows start at a multiple of
-  // kScanMPs * kRowCap * 4 bytes, and a row's kRowCap ids fill whole pieces)
-  static_assert(kScanMPs < 256, "one row start per thread");
-  static_assert(kRowCap % 4 == 0, "rows of whole 16-byte pieces");
-  constexpr int kPieces = kScanMPs * kRowCap / 4;
-  constexpr int kPer = (kPieces + 255) / 256;
-  const int64_t my_off = tid <= nloc ? offsets[p0 + tid] : 0;
-  const int64_t total_pairs = offsets[n_mp];
-  const int4* __restrict__ st4 = reinterpret_cast<const int4*>(stage + p0 * kRowCap);
-  int4* rows4 = reinterpret_cast<int4*>(rows);
-  const int npc = nloc * (kRowCap / 4);
-  int4 st[kPer];
+  const int32_t mine = lane < nloc ? cnt[p0 + lane] : 0;
+  int64_t start, total_pairs;
+  if (!DIRECT) {
+    start = runs[p0 / kPairRun].pairs + group[blk];
+    total_pairs = runs[n_runs].pairs;
+  }
+  const int i = kWaveRows * w + lane / 4;  // this quad's row
+  const int32_t K = __shfl(mine, i);
+  const int32_t staged = K <= kRowCap ? K : 0;
+  const int32_t* __restrict__ row = stage + (p0 + i) * kRowCap;
+  const bool wide = __ballot(staged > 32) != 0;
+  int32_t a[8];
+  if (!wide) load_row_quad<8>(a, row, staged, l);
+  if (DIRECT) {
+    __shared__ int64_t sum_before[4], sum_all[4];
+    __shared__ int32_t most_of[4];
+    int64_t before = 0, all = 0;
+    int32_t most = 0;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int i = k * 256 + tid;
-    st[k] = i < npc ? st4[i] : make_int4(0, 0, 0, 0);
-  }
-  if (tid <= nloc) off[tid] = my_off;
+    for (int k = 0; k < kDirectMPs / 1024; ++k) {
+      const int64_t q = (k * 256 + tid) * 4;
+      const int4 v = load_counts(cnt, q, n_mp);
+      const int32_t c[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int i = k * 256 + tid;
-    if (i < npc) rows4[i] = st[k];
-  }
-  __syncthreads();
-  // largest support of the workgroup (reduced once more by k_search_done;
-  // one atomic per MP on a single counter would serialise the pass)
-  if (tid < kWave) {
-    int32_t m = 0;
-    for (int i = tid; i < nloc; i += kWave) {
-      const int32_t K = (int32_t)(off[i + 1] - off[i]);
-      m = K > m ? K : m;
-    }
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-      const int32_t u = __shfl_xor(m, o);
-      m = u > m ? u : m;
-    }
-    if (tid == 0) {
-      block_max[blk] = m;
-      blk_max = m;
-    }
-  }
-  if (total_pairs > capacity) return;  // lists do not fit: counts only
-  // the staged rows come in stencil order: the four lanes of quad i sort row
-  // i (rows past 32 ids, rare, by insertion in LDS in the quad's first lane;
-  // rows past kRowCap are re-found below)
-  static_assert(4 * kScanMPs == 256, "one quad per staged row");
-  if (tid / 4 < nloc) {
-    const int i = tid / 4, l = tid % 4;
-    const int K = (int)(off[i + 1] - off[i]);
-    int32_t* row = rows + i * kRowCap;
-    if (K <= 32) {
-      sort_row32_quad(row, K, l);
-    } else if (K <= kRowCap && l == 0) {
-      for (int j = 1; j < K; ++j) {
-        const int32_t id = row[j];
-        int t = j;
-        for (; t > 0 && row[t - 1] > id; --t) row[t] = row[t - 1];
-        row[t] = id;
+      for (int e = 0; e < 4; ++e) {
+        all += c[e];
+        before += q + e < p0 ? c[e] : 0;
+        most = max(most, c[e]);
       }
     }
-  }
-  __syncthreads();
-  const int64_t base = off[0];
-  const int total = (int)(off[nloc] - base);
-  if (blk_max <= kRowCap) {
-    // every row is staged: mark the MP of each output element, then copy
-    // with unit-stride stores
-    for (int t = tid; t < nloc * kRowCap; t += 256) {
-      const int i = t / kRowCap, j = t - i * kRowCap;
-      if (j < (int)(off[i + 1] - off[i])) owner[(int)(off[i] - base) + j] = (uint8_t)i;
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+      before += __shfl_xor(before, o);
+      all += __shfl_xor(all, o);
+    }
+    most = wave_max(most);
+    if (lane == 0) {
+      sum_before[w] = before;
+      sum_all[w] = all;
+      most_of[w] = most;
     }
     __syncthreads();
-    for (int e = tid; e < total; e += 256) {
-      const int i = owner[e];
-      idx[base + e] = rows[i * kRowCap + (e - (int)(off[i] - base))];
+    start = (sum_before[0] + sum_before[1]) + (sum_before[2] + sum_before[3]);
+    total_pairs = (sum_all[0] + sum_all[1]) + (sum_all[2] + sum_all[3]);
+    if (blk == 0 && tid == 0 && diag != nullptr) {
+      diag->pairs_needed = total_pairs;
+      diag->max_support = max(max(most_of[0], most_of[1]), max(most_of[2], most_of[3]));
+      if (total_pairs > capacity) atomicOr(&diag->flags, 1u << (-OTM_ERR_CAPACITY - 1));
     }
+  }
+  int64_t excl = mine;  // pairs of the group before this lane's MP
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int64_t u = __shfl_up(excl, o);
+    excl += lane >= o ? u : 0;
+  }
+  if (w == 0) {
+    if (lane < nloc) offsets[p0 + lane] = start + excl - mine;
+    if (lane == nloc - 1 && p0 + nloc == n_mp) offsets[n_mp] = start + excl;
+  }
+  if (total_pairs > capacity) return;  // lists do not fit: row starts only
+  excl -= mine;
+  const int64_t seg = start + __shfl(excl, kWaveRows * w);  // the wave's first pair
+  const int64_t o = start + __shfl(excl, i);                // the row's
+  // image of the wave's segment; with a row past kRowCap, straight to memory
+  const bool fits = __ballot(K > kRowCap) == 0;
+  int32_t* img = image[w];
+  if (!wide) {
+    sort_row_quad<8>(a, l);
+    if (fits) put_row_quad<8>(a, img + (int)(o - seg), staged, l);
+    else put_row_quad<8>(a, idx + o, staged, l);
+  } else {
+    int32_t b[16];
+    load_row_quad<16>(b, row, staged, l);
+    sort_row_quad<16>(b, l);
+    if (fits) put_row_quad<16>(b, img + (int)(o - seg), staged, l);
+    else put_row_quad<16>(b, idx + o, staged, l);
+  }
+  if (fits) {
+    const int total = (int)(__shfl(o, kWave - 1) - seg) + __shfl(K, kWave - 1);
+    // one wave writes and reads the image: its LDS accesses run in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int e = lane; e < total; e += kWave) idx[seg + e] = img[e];
     return;
   }
-  for (int e = tid; e < total; e += 256) {
-    // MP of output element e: last t with off[t] - base <= e
-    int lo = 0, hi = nloc - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (off[mid] - base <= e) lo = mid; else hi = mid - 1;
-    }
-    const int K = (int)(off[lo + 1] - off[lo]);
-    if (K <= kRowCap) idx[base + e] = rows[lo * kRowCap + (e - (int)(off[lo] - base))];
-  }
   // long supports
-  if (tid < nloc && off[tid + 1] - off[tid] > kRowCap) {
-    const int64_t p = p0 + tid;
-    const int64_t o = off[tid];
+  if (l == 0 && K > kRowCap) {
+    const int64_t p = p0 + i;
     const Grid g = *gp;
     int32_t n = 0;
     for_each_neighbor(xp[p], xp[n_mp + p], xp[2 * n_mp + p], r2, g, cell_start, sorted,
@@ -757,72 +958,64 @@ __global__ __launch_bounds__(256) void k_nbr_compact(
   }
 }
 
-__global__ void k_set_first_offset(int64_t* offsets) { offsets[0] = 0; }
-
-__global__ __launch_bounds__(1024) void k_search_done(const int64_t* offsets, int64_t n_mp,
-                                                      const int32_t* block_max, int64_t nblocks,
-                                                      int64_t capacity, otm_diag* diag) {
-  __shared__ int32_t red[1024 / kWave];
-  // the total is requested first, and the maxima eight at a time, so the
-  // loads overlap instead of following one another
-  const int64_t P = threadIdx.x == 0 ? offsets[n_mp] : 0;
-  int32_t m = 0;
-  int64_t b = threadIdx.x;
-  for (; b + 7 * 1024 < nblocks; b += 8 * 1024) {
-    int32_t v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = block_max[b + k * 1024];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m = v[k] > m ? v[k] : m;
+// No MPs: one row start and nothing found.
+__global__ void k_search_empty(int64_t* offsets, otm_diag* diag) {
+  offsets[0] = 0;
+  if (diag != nullptr) {
+    diag->pairs_needed = 0;
+    diag->max_support = 0;
   }
-  for (; b < nblocks; b += 1024) m = block_max[b] > m ? block_max[b] : m;
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    const int32_t u = __shfl_xor(m, o);
-    m = u > m ? u : m;
-  }
-  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = m;
-  __syncthreads();
-  if (threadIdx.x != 0 || diag == nullptr) return;
-  for (int w = 1; w < 1024 / kWave; ++w) m = red[w] > m ? red[w] : m;
-  diag->pairs_needed = P;
-  diag->max_support = m;
-  if (P > capacity) atomicOr(&diag->flags, 1u << (-OTM_ERR_CAPACITY - 1));
 }
 
 void launch_search(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
                    double r_list, double cell_size, int64_t pair_capacity, int64_t* nbr_offsets,
                    int32_t* nbr_idx, const Workspace& w, otm_diag* diag, hipStream_t s) {
-  const BinCounters z{w.cell_start, w.cell_cursor, w.mp_cell_start, w.mp_cell_cursor,
-                      w.cap_cells};
-  k_bbox_partial<<<kBBoxBlocks, 256, 0, s>>>(x_nodes, n_nodes, w.bbox_part, z);
-  k_grid_finalize<<<1, 256, 0, s>>>(w.bbox_part, kBBoxBlocks, cell_size, w.cap_cells, w.grid);
+  if (n_mp <= 0) {
+    k_search_empty<<<1, 1, 0, s>>>(nbr_offsets, diag);
+    return;
+  }
+  const BinCounters z{w.cell_start, w.mp_cell_start, w.cap_cells, w.ticket};
+  Box* part = reinterpret_cast<Box*>(w.bbox_part);
+  const unsigned n_part = bbox_blocks(n_nodes);
+  k_bbox_partial<<<n_part, 256, 0, s>>>(x_nodes, n_nodes, part, z);
   // nodes and MPs binned on the grid together: one count, one two-array scan,
-  // one fill
-  const BinSet nodes{x_nodes, n_nodes, w.node_cell, w.cell_start, w.cell_cursor, w.sorted};
-  const BinSet mps{x_mp, n_mp, w.mp_cell, w.mp_cell_start, w.mp_cell_cursor, w.mp_sorted};
+  // one fill.  The MPs' ranks lie where their rows are staged later.
+  const BinSet nodes{x_nodes, n_nodes, w.node_cell, w.node_rank, w.cell_start, w.sorted};
+  const BinSet mps{x_mp, n_mp, w.mp_cell, w.stage, w.mp_cell_start, w.mp_sorted};
   const int64_t b0 = (n_nodes + kWave - 1) / kWave * kWave;
   const int64_t nt = b0 + n_mp;
   const unsigned nbt = (unsigned)((nt + 255) / 256);
-  if (nbt > 0) k_bin_count<<<nbt, 256, 0, s>>>(nodes, mps, b0, w.grid);
-  scan_impl<int32_t>(w.cell_start + 1, w.mp_cell_start + 1, w.cap_cells, w.scan_aux, s);
-  if (nbt > 0) k_bin_fill<<<nbt, 256, 0, s>>>(nodes, mps, b0);
+  k_bin_count<<<nbt < kCountBlocks ? nbt : kCountBlocks, 256, 0, s>>>(
+      nodes, mps, b0, part, (int)n_part, cell_size, w.cap_cells, w.grid);
+  scan_impl<int32_t>(w.cell_start + 1, w.mp_cell_start + 1, w.cap_cells, w.scan_aux,
+                     &w.grid->n_cells, s);
+  k_bin_fill<<<nbt, 256, 0, s>>>(nodes, mps, b0);
   const double r2 = r_list * r_list;
-  if (n_mp > 0) {
-    // a fixed grid (a multiple of the 8 XCDs) strides over the cells
-    k_cell_scan<<<kCellBlocks, kCellWaves * kWave, 0, s>>>(r2, w.grid, w.cap_cells, w.cell_start,
-                                                   w.sorted, w.mp_cell_start, w.mp_sorted,
-                                                   nbr_offsets, w.stage);
-    scan_inclusive(nbr_offsets + 1, n_mp, w.scan_aux, s);
-    const unsigned nbs = (unsigned)((n_mp + kScanMPs - 1) / kScanMPs);
-    k_nbr_compact<<<nbs, 256, 0, s>>>(x_mp, n_mp, r2, w.grid, w.cell_start, w.sorted,
-                                      nbr_offsets, w.stage, pair_capacity, nbr_idx,
-                                      w.block_max);
-  } else {
-    k_set_first_offset<<<1, 1, 0, s>>>(nbr_offsets);
+  // a fixed grid (a multiple of the 8 XCDs) strides over the items.  The MPs'
+  // cells are not needed any more: their counts take that place.
+  const int64_t most = w.cap_cells > 2 * kMinItems ? w.cap_cells : 2 * kMinItems;
+  const int64_t want = (most + kCellWaves - 1) / kCellWaves;
+  const unsigned cells = want < kCellBlocks ? (unsigned)((want + 7) / 8 * 8) : kCellBlocks;
+  int32_t* cnt = w.mp_cell;
+  k_cell_scan<<<cells, kCellWaves * kWave, 0, s>>>(r2, w.grid, w.cap_cells, w.cell_start,
+                                                   w.sorted, w.mp_cell_start, w.mp_sorted, cnt,
+                                                   w.stage);
+  const unsigned nbs = (unsigned)((n_mp + kScanMPs - 1) / kScanMPs);
+  if (n_mp <= kDirectMPs) {
+    k_nbr_compact<true><<<nbs, 256, 0, s>>>(x_mp, n_mp, r2, w.grid, w.cell_start, w.sorted, cnt,
+                                            nullptr, nullptr, 0, nbr_offsets, w.stage,
+                                            pair_capacity, nbr_idx, diag);
+    return;
   }
-  const int64_t nbs_all = (n_mp + kScanMPs - 1) / kScanMPs;
-  k_search_done<<<1, 1024, 0, s>>>(nbr_offsets, n_mp, w.block_max, nbs_all, pair_capacity,
-                                   diag);
+  // the binned MPs are not needed any more either: the runs' totals and the
+  // groups' places, which are far smaller, take their place
+  const int64_t n_runs = (n_mp + kPairRun - 1) / kPairRun;
+  PairRun* runs = reinterpret_cast<PairRun*>(w.mp_sorted);
+  int64_t* group = reinterpret_cast<int64_t*>(runs + n_runs + 1);
+  k_pair_runs<<<(unsigned)n_runs, 1024, 0, s>>>(cnt, n_mp, group, runs, w.ticket, pair_capacity, diag);
+  k_nbr_compact<false><<<nbs, 256, 0, s>>>(x_mp, n_mp, r2, w.grid, w.cell_start, w.sorted, cnt,
+                                           group, runs, n_runs, nbr_offsets, w.stage,
+                                           pair_capacity, nbr_idx, diag);
 }
 
 }  // namespace otm
