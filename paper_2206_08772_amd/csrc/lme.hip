@@ -564,10 +564,11 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
 }
 
 // The pipelined kernel pays off from four rounds per workgroup on; below, its
-// first pass and its fixed grid cost more than the overlap gives.  OTM_MIXED
-// stays here whatever the size: its float32 return map turns a last-bit change
-// of grad N into 1e-6 of a point's stress, so its results keep this kernel's
-// order of operations.
+// first pass and its fixed grid cost more than the overlap gives.  It is for
+// OTM_FP64 alone: float32 values amplify a last-bit change of N or grad N (the
+// return map of OTM_MIXED turns it into 1e-6 of a point's stress, the storage
+// of OTM_MIXED_STORAGE into 6e-8 where it moves a value over a rounding
+// boundary), so their results keep this kernel's order of operations.
 constexpr int64_t kPipelinedMps = 4 * 512 * 64;
 
 void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
@@ -576,9 +577,9 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
                 int32_t precision, const double4* packed, otm_diag* diag, hipStream_t s,
                 const AsmIn* fused, const SegIn* seg) {
   if (n_mp <= 0) return;
-  if (precision != OTM_MIXED && n_mp >= kPipelinedMps) {
+  if (precision == OTM_FP64 && n_mp >= kPipelinedMps) {
     launch_lme_pipelined(n_nodes, x_nodes, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
-                         tol, max_iter, lam, N, dN, precision, packed, diag, s, fused, seg);
+                         tol, max_iter, lam, N, (double*)dN, packed, diag, s, fused, seg);
     return;
   }
   const NodeSrc ns{x_nodes, packed, n_nodes};

@@ -202,11 +202,10 @@ struct NoSink {
 };
 
 // An MP's mass, volume and stress.
-template <typename R>
 struct MpForce {
   double mp, vd;
-  R s0, s1, s2, s3, s4, s5;
-  OTM_DEV void load(const double* mass, const double* vol, const R* sigma, int64_t n_mp,
+  double s0, s1, s2, s3, s4, s5;
+  OTM_DEV void load(const double* mass, const double* vol, const double* sigma, int64_t n_mp,
                     int64_t p) {
     mp = mass[p];
     vd = vol[p];
@@ -221,12 +220,11 @@ struct MpForce {
 
 // Fused nodal assembly (nodal mass and residual equations, Sec. 2.1): the
 // pair's m and f contributions, with the same arithmetic as the standalone
-// assembly kernel (grad N rounded to its stored type R first), go into the
-// workgroup's node table.  With conduction (HEAT) the table also sums
-// N m_p T_p and v_p q_p . grad N (float64, grad N rounded the same way).
+// assembly kernel, go into the workgroup's node table.  With conduction (HEAT)
+// the table also sums N m_p T_p and v_p q_p . grad N.
 // The table slots of the lane's nodes are claimed before the Newton solve, all
 // probes in flight together; the sums then need no LDS round trip.
-template <typename R, bool HEAT, typename Q>
+template <bool HEAT>
 struct AsmSink {
   static constexpr int V = HEAT ? 6 : 4;
   struct In {
@@ -238,17 +236,17 @@ struct AsmSink {
     uint16_t slots[4 * kPpl * kWave];  // the waves' table slots (0xFFFF: none)
   };
   static constexpr bool kTable = true;
-  struct Mp : MpForce<R> {
+  struct Mp : MpForce {
     double T, q0, q1, q2;
     OTM_DEV void load(const In& in, int64_t n_mp, int64_t p) {
-      MpForce<R>::load(in.a.mass, in.a.vol, (const R*)in.a.sigma, n_mp, p);
+      MpForce::load(in.a.mass, in.a.vol, (const double*)in.a.sigma, n_mp, p);
       if constexpr (HEAT) {
         T = in.a.T[p];
         q0 = in.a.q[p]; q1 = in.a.q[n_mp + p]; q2 = in.a.q[2 * n_mp + p];
       }
     }
     OTM_DEV void ready() const {
-      MpForce<R>::ready();
+      MpForce::ready();
       if constexpr (HEAT) { hold(T); hold(q0); hold(q1); hold(q2); }
     }
   };
@@ -319,12 +317,11 @@ struct AsmSink {
     wave_order();
   }
   OTM_DEV static void values(const Mp& m, double Nq, const double* g, double (&c)[V]) {
-    const R g0 = (R)g[0], g1 = (R)g[1], g2 = (R)g[2];
     c[0] = Nq * m.mp;
-    pair_force<Q>(m.vd, m.s0, m.s1, m.s2, m.s3, m.s4, m.s5, g0, g1, g2, c[1], c[2], c[3]);
+    pair_force<double>(m.vd, m.s0, m.s1, m.s2, m.s3, m.s4, m.s5, g[0], g[1], g[2], c[1], c[2], c[3]);
     if constexpr (HEAT) {
       c[4] = c[0] * m.T;
-      c[5] = m.vd * ((m.q0 * (double)g0 + m.q1 * (double)g1) + m.q2 * (double)g2);
+      c[5] = m.vd * ((m.q0 * g[0] + m.q1 * g[1]) + m.q2 * g[2]);
     }
   }
   OTM_DEV void add_row(const In& in, const Mp& m, const Slots& sl, int64_t q,
@@ -362,14 +359,13 @@ struct AsmSink {
 // Fused contribution store of the deterministic assembly: the pair's four
 // contributions (the standalone contribution kernel's arithmetic) go to its
 // place in the node-sorted order, where each node later sums them in order.
-template <typename R, typename Q>
 struct SegSink {
   using In = SegIn;
   using Table = NoTable;
   static constexpr bool kTable = false;
-  struct Mp : MpForce<R> {
+  struct Mp : MpForce {
     OTM_DEV void load(const In& in, int64_t n_mp, int64_t p) {
-      MpForce<R>::load(in.mass, in.vol, (const R*)in.sigma, n_mp, p);
+      MpForce::load(in.mass, in.vol, (const double*)in.sigma, n_mp, p);
     }
   };
   OTM_DEV void setup(Table&) {}
@@ -381,16 +377,15 @@ struct SegSink {
     });
   }
   OTM_DEV void add(const In& in, const Mp& m, int64_t q, double Nq, const double* g) {
-    const R g0 = (R)g[0], g1 = (R)g[1], g2 = (R)g[2];
     double c1, c2, c3;
-    pair_force<Q>(m.vd, m.s0, m.s1, m.s2, m.s3, m.s4, m.s5, g0, g1, g2, c1, c2, c3);
+    pair_force<double>(m.vd, m.s0, m.s1, m.s2, m.s3, m.s4, m.s5, g[0], g[1], g[2], c1, c2, c3);
     in.contrib[in.pos_of[q]] = make_double4(Nq * m.mp, c1, c2, c3);
   }
   OTM_DEV void flush(const In&, int) {}
 };
 
 // Everything an MP's solve reads and writes.
-template <typename DN, bool PACKED>
+template <bool PACKED>
 struct LmeArgs {
   NodeSrc<PACKED> ns;
   int64_t n_mp;
@@ -402,7 +397,7 @@ struct LmeArgs {
   int max_iter;
   double* __restrict__ lam;
   double* __restrict__ N;
-  DN* __restrict__ dN;
+  double* __restrict__ dN;
   otm_diag* diag;
 };
 
@@ -504,8 +499,8 @@ OTM_DEV Solve lme_solve(const double (&d)[kPpl][3], double (&e)[kPpl], const Slo
 
 // One MP's solve with its pairs re-read from memory at every evaluation, and
 // its stores.
-template <typename DN, bool PACKED, class Sink>
-OTM_DEV void lme_uncached(const LmeArgs<DN, PACKED>& a, const typename Sink::In& in, int64_t p,
+template <bool PACKED, class Sink>
+OTM_DEV void lme_uncached(const LmeArgs<PACKED>& a, const typename Sink::In& in, int64_t p,
                           int lane, int64_t off, int K, Sink& sink) {
   const int64_t n_mp = a.n_mp;
   const double px = a.xp[p], py = a.xp[n_mp + p], pz = a.xp[2 * n_mp + p];
@@ -569,9 +564,9 @@ OTM_DEV void lme_uncached(const LmeArgs<DN, PACKED>& a, const typename Sink::In&
     sym_mul_vec(Mi, d3, g);
     g[0] *= -Nq; g[1] *= -Nq; g[2] *= -Nq;
     a.N[off + q] = Nq;
-    a.dN[off + q] = (DN)g[0];
-    a.dN[a.cap + off + q] = (DN)g[1];
-    a.dN[2 * a.cap + off + q] = (DN)g[2];
+    a.dN[off + q] = g[0];
+    a.dN[a.cap + off + q] = g[1];
+    a.dN[2 * a.cap + off + q] = g[2];
     sink.add(in, mp, off + q, Nq, g);
   }
 }
@@ -595,27 +590,20 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // rounded-down start) of one array from LDS: kPieces stores of two entries
 // per lane, then the entries without a partner (an odd start in lane 0, an odd
 // end in lane 1).  Every lane and instruction is always issued.
-template <typename T>
-OTM_DEV void store_run(T* base, const T* st, int lane, int front, int end) {
+OTM_DEV void store_run(double* base, const double* st, int lane, int front, int end) {
   const __amdgpu_buffer_rsrc_t rs = buffer_at((void*)first_lane((int64_t)base));
 #pragma unroll
   for (int i = 0; i < kPieces; ++i) {
     const int e = 2 * (kWave * i + lane);
     const bool full = e >= front && e + 1 < end;
-    const int o = full ? e * (int)sizeof(T) : (int)kDrop;
-    if constexpr (sizeof(T) == 8)
-      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(st + e), rs, o, 0, 0);
-    else
-      __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(st + e), rs, o, 0, 0);
+    const int o = full ? e * (int)sizeof(double) : (int)kDrop;
+    __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(st + e), rs, o, 0, 0);
   }
   const bool odd = (lane == 0 && front == 1 && front < end) ||
                    (lane == 1 && (end & 1) != 0 && end - 1 >= front && !(front == 1 && end == 1));
   const int e = lane == 0 ? 1 : (end > 0 ? end - 1 : 0);
-  const int o = odd ? e * (int)sizeof(T) : (int)kDrop;
-  if constexpr (sizeof(T) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(st + e), rs, o, 0, 0);
-  else
-    __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t*>(st + e), rs, o, 0, 0);
+  const int o = odd ? e * (int)sizeof(double) : (int)kDrop;
+  __builtin_amdgcn_raw_buffer_store_b64(*reinterpret_cast<const u32x2*>(st + e), rs, o, 0, 0);
 }
 
 // Workgroup barrier that orders LDS only: __syncthreads() would also wait for
@@ -654,9 +642,9 @@ inline int lme_chunk(int64_t n_mp) {
   return per_wg >= 4 * 512 ? 512 : (int)per_wg;
 }
 
-template <typename DN, bool PACKED, class Sink>
+template <bool PACKED, class Sink>
 struct LmeCall {
-  LmeArgs<DN, PACKED> a;
+  LmeArgs<PACKED> a;
   typename Sink::In in;
   int chunk;
 };
@@ -670,9 +658,9 @@ OTM_DEV const T& kernel_arg() {
   return *(const T*)p;
 }
 
-template <typename DN, bool PACKED, class Sink>
-__global__ __launch_bounds__(256, 2) void k_lme(LmeCall<DN, PACKED, Sink> call) {
-  using Call = LmeCall<DN, PACKED, Sink>;
+template <bool PACKED, class Sink>
+__global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
+  using Call = LmeCall<PACKED, Sink>;
   __shared__ typename Sink::Table table;
   __shared__ __align__(16) double stage[4][kStage + 2];
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -813,9 +801,9 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<DN, PACKED, Sink> call) 
         if (q < K0) {
           const int64_t at = even0 + (rel0 + q);
           c1.a.N[at] = e[k];
-          c1.a.dN[at] = (DN)d[k][0];
-          c1.a.dN[c1.a.cap + at] = (DN)d[k][1];
-          c1.a.dN[2 * c1.a.cap + at] = (DN)d[k][2];
+          c1.a.dN[at] = d[k][0];
+          c1.a.dN[c1.a.cap + at] = d[k][1];
+          c1.a.dN[2 * c1.a.cap + at] = d[k][2];
         }
       }
     }
@@ -861,13 +849,12 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<DN, PACKED, Sink> call) 
     const int64_t off2 = o2[0], end2 = o2[1];
     __builtin_amdgcn_sched_barrier(0);
     const int end = run ? end0 : 0;
-    store_run<double>(c2.a.N + even0, st, wl, front0, end);
-    DN* const sd = reinterpret_cast<DN*>(st);
+    store_run(c2.a.N + even0, st, wl, front0, end);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       __builtin_amdgcn_sched_barrier(0);
-      put(sd, [&](int k) { return d[k][c]; });
-      store_run<DN>(c2.a.dN + c * c2.a.cap + even0, sd, wl, front0, end);
+      put(st, [&](int k) { return d[k][c]; });
+      store_run(c2.a.dN + c * c2.a.cap + even0, st, wl, front0, end);
     }
     // (both words of each bound, so that no register of the loads is reused
     // while they are under way, which would wait for them before the stores)
@@ -915,8 +902,7 @@ struct Type {
 void launch_lme_pipelined(int64_t n_nodes, const double* x_nodes, int64_t n_mp,
                           const double* x_mp, const int64_t* nbr_offsets, const int32_t* nbr_idx,
                           int64_t pair_capacity, double beta, double tol, int32_t max_iter,
-                          double* lam, double* N, void* dN, int32_t precision,
-                          const double4* packed, otm_diag* diag, hipStream_t s,
+                          double* lam, double* N, double* dN, const double4* packed, otm_diag* diag, hipStream_t s,
                           const AsmIn* fused, const SegIn* seg) {
   if (n_mp <= 0) return;
   const int chunk = lme_chunk(n_mp);
@@ -927,37 +913,27 @@ void launch_lme_pipelined(int64_t n_nodes, const double* x_nodes, int64_t n_mp,
     if (packed != nullptr) packed = (const double4*)x_mp;
   }
   if (pair_capacity <= 0) nbr_idx = (const int32_t*)nbr_offsets;
-  auto run = [&](auto* dn, auto tag, auto pk, auto in) {
-    using DN = std::remove_pointer_t<decltype(dn)>;
+  auto run = [&](auto tag, auto pk, auto in) {
     using Sink = typename decltype(tag)::type;
     constexpr bool PACKED = decltype(pk)::value;
-    const LmeCall<DN, PACKED, Sink> call{
-        LmeArgs<DN, PACKED>{NodeSrc<PACKED>{x_nodes, packed, n_nodes}, n_mp, x_mp, nbr_offsets,
-                            nbr_idx, pair_capacity, beta, tol, max_iter, lam, N, dn, diag},
+    const LmeCall<PACKED, Sink> call{
+        LmeArgs<PACKED>{NodeSrc<PACKED>{x_nodes, packed, n_nodes}, n_mp, x_mp, nbr_offsets,
+                        nbr_idx, pair_capacity, beta, tol, max_iter, lam, N, dN, diag},
         in, chunk};
-    k_lme<DN, PACKED, Sink><<<kLmeBlocks, 256, 0, s>>>(call);
+    k_lme<PACKED, Sink><<<kLmeBlocks, 256, 0, s>>>(call);
   };
   // (the step's calls, the ones with a sink, always bring node records)
-  auto pick = [&](auto* dn, auto q_tag) {
-    using DN = std::remove_pointer_t<decltype(dn)>;
-    using Q = decltype(q_tag);
-    using Heat = AsmSink<DN, true, Q>;
-    using Asm = AsmSink<DN, false, Q>;
-    using Seg = SegSink<DN, Q>;
-    constexpr std::true_type yes;
-    if (fused != nullptr && fused->heat != nullptr)
-      run(dn, Type<Heat>{}, yes, typename Heat::In{*fused, nbr_idx});
-    else if (fused != nullptr)
-      run(dn, Type<Asm>{}, yes, typename Asm::In{*fused, nbr_idx});
-    else if (seg != nullptr)
-      run(dn, Type<Seg>{}, yes, *seg);
-    else if (packed != nullptr)
-      run(dn, Type<NoSink>{}, yes, NoSink::In{});
-    else
-      run(dn, Type<NoSink>{}, std::false_type{}, NoSink::In{});
-  };
-  if (precision == OTM_FP64) pick((double*)dN, double{});
-  else pick((float*)dN, double{});
+  constexpr std::true_type yes;
+  if (fused != nullptr && fused->heat != nullptr)
+    run(Type<AsmSink<true>>{}, yes, AsmSink<true>::In{*fused, nbr_idx});
+  else if (fused != nullptr)
+    run(Type<AsmSink<false>>{}, yes, AsmSink<false>::In{*fused, nbr_idx});
+  else if (seg != nullptr)
+    run(Type<SegSink>{}, yes, *seg);
+  else if (packed != nullptr)
+    run(Type<NoSink>{}, yes, NoSink::In{});
+  else
+    run(Type<NoSink>{}, std::false_type{}, NoSink::In{});
 }
 
 }  // namespace otm
