@@ -211,7 +211,7 @@ static void refresh_impl(otm_state& st, const otm_params& p, bool rebuild, int32
   const SegIn seg{st.vol, st.mass, st.sigma, w.tr_pos, w.contrib};
   launch_lme(st.n_nodes, st.x, st.n_mp, st.xp, st.nbr_offsets, st.nbr_idx, st.pair_capacity,
              p.beta, p.lme_tol, p.lme_max_iter, st.lam, st.N, st.dN, st.precision, w.nodes, diag,
-             s, fuse_atomic ? &fused : nullptr, fuse_seg ? &seg : nullptr);
+             s, fuse_atomic ? &fused : nullptr, fuse_seg ? &seg : nullptr, !rebuild);
   if (fuse_seg) {
     mark(ev, 5, s);
     launch_seg_gather(st, w, s);

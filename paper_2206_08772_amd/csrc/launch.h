@@ -90,11 +90,12 @@ struct SegIn {
 // ``packed`` (nullable): node records (x, y, z, du_x) at even indices.
 // ``fused`` (nullable): also assemble m and f from the new N and grad N.
 // ``seg`` (nullable): also store every pair's contributions in node order.
+// ``kept``: the lists are of an earlier step (they carry a skin: longer rows).
 void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
                 const int64_t* nbr_offsets, const int32_t* nbr_idx, int64_t pair_capacity,
                 double beta, double tol, int32_t max_iter, double* lam, double* N, void* dN,
                 int32_t precision, const double4* packed, otm_diag* diag, hipStream_t s,
-                const AsmIn* fused = nullptr, const SegIn* seg = nullptr);
+                const AsmIn* fused = nullptr, const SegIn* seg = nullptr, bool kept = false);
 
 // Nodes and material points.
 // Node records: packed[2 I] = (x, y, z, du_x), packed[2 I + 1] = (du_y, du_z,

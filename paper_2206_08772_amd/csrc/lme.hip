@@ -21,6 +21,8 @@
 // with sufficient-decrease factor 1e-4 plus a round-off allowance
 // 1e-12 (1 + |log Z|), up to 30 halvings; stop at |r|_2 <= tol.  Gradients
 // dN_I = -N_I J^{-1} d_I at the converged multiplier.
+#include <type_traits>
+
 #include "launch.h"
 #include "lme.h"
 #include "otm_common.h"
@@ -455,7 +457,8 @@ __global__ __launch_bounds__(256) void k_lme(NodeSrc ns, int64_t n_mp, const dou
 // 256 / G (a chunk's last round may be partial); the node table is flushed
 // to m and f every kLmeAsmFlushRounds rounds and at the end of each chunk.
 // The round count is the same for every lane of a workgroup, so the barriers
-// around a flush are reached by all of them.
+// around a flush are reached by all of them.  Rows of more than G * PPL pairs
+// take the uncached solve in their round, or (LEAVE) after the last one.
 constexpr int kLmeAsmBlocks = 512;
 constexpr int kLmeAsmFlushRounds = 8;
 static_assert(kLmeAsmBlocks % 8 == 0, "the workgroups split evenly over the 8 XCDs");
@@ -469,7 +472,7 @@ inline int64_t lme_asm_chunk(int64_t n_mp) {
   return per_wg >= 4 * 512 ? 512 : per_wg;
 }
 
-template <int G, int PPL, typename DN, bool HEAT, typename Q>
+template <int G, int PPL, bool LEAVE, typename DN, bool HEAT, typename Q>
 __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
                                                  const double* __restrict__ xp,
                                                  const int64_t* __restrict__ offsets,
@@ -527,6 +530,7 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
   auto fetch = [&]() { load_row_ids<G, PPL>(nxt, idx, lane); };
   auto wait = [&]() { hold_row(nxt); };
   const MidHooks<decltype(fetch), decltype(wait)> mid{fetch, wait};
+  bool some_left = false;
   int64_t c = c_lo + j, k = 0;
   row_at(c, 0, nxt);
   fetch();
@@ -539,12 +543,17 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
     const int64_t cn = chunk_end ? c + wgs : c, kn = chunk_end ? 0 : k + 1;
     row_at(cn, kn, nxt);
     if (ok && i < chunk && p < n_mp) {
-      if (cur.K <= G * PPL)
+      if (cur.K <= G * PPL) {
         lme_point<G, PPL, true, DN>(p, lane, ns, n_mp, xp, offsets, idx, cap, beta, tol,
                                     max_iter, lam, N, dN, diag, sink, &cur, mid);
-      else
+      } else if constexpr (LEAVE) {
+        some_left = true;
+        mid();
+        mid.ready();
+      } else {
         lme_point<G, PPL, false, DN>(p, lane, ns, n_mp, xp, offsets, idx, cap, beta, tol,
                                      max_iter, lam, N, dN, diag, sink, &cur, mid);
+      }
     }
     // a lane without an MP this round (past its chunk's end, or past the last
     // MP) has an empty next row: the next round is further on in the same
@@ -558,6 +567,43 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
     }
     c = cn;
     k = kn;
+  }
+  // the long rows of the workgroup's chunks, collected and solved per_round at
+  // a time: in place, a wave with one such row takes a whole round more
+  if (LEAVE && __syncthreads_or(some_left)) {
+    __shared__ int64_t queue[256 + per_round];
+    __shared__ int added[256 / kWave];
+    int n = 0, batches = 0;  // the same in every lane
+    auto solve = [&](int rows) {
+      n -= rows;
+      if (tid / G < rows)
+        lme_point<G, PPL, false, DN>(queue[n + tid / G], lane, ns, n_mp, xp, offsets, idx, cap,
+                                     beta, tol, max_iter, lam, N, dN, diag, sink);
+      __syncthreads();
+      if (++batches % kLmeAsmFlushRounds == 0) {
+        table_flush(table, tid, 256, dst);
+        __syncthreads();
+      }
+    };
+    for (c = c_lo + j; c < c_hi; c += wgs) {
+      for (int64_t i0 = 0; i0 < chunk; i0 += 256) {
+        const int64_t q = c * chunk + i0 + tid;
+        const bool is_long =
+            i0 + tid < chunk && q < n_mp && offsets[q + 1] - offsets[q] > G * PPL;
+        const uint64_t votes = __ballot(is_long);
+        if (tid % kWave == 0) added[tid / kWave] = __popcll(votes);
+        __syncthreads();
+        int at = n + __popcll(votes & ((1ull << (tid % kWave)) - 1));
+        for (int w = 0; w < 256 / kWave; ++w) {
+          at += w < tid / kWave ? added[w] : 0;
+          n += added[w];
+        }
+        if (is_long) queue[at] = q;
+        __syncthreads();
+        while (n >= per_round) solve(per_round);
+      }
+    }
+    if (n > 0) solve(n);
   }
   __syncthreads();
   table_flush(table, tid, 256, dst);
@@ -575,7 +621,7 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
                 const int64_t* nbr_offsets, const int32_t* nbr_idx, int64_t pair_capacity,
                 double beta, double tol, int32_t max_iter, double* lam, double* N, void* dN,
                 int32_t precision, const double4* packed, otm_diag* diag, hipStream_t s,
-                const AsmIn* fused, const SegIn* seg) {
+                const AsmIn* fused, const SegIn* seg, bool kept) {
   if (n_mp <= 0) return;
   if (precision == OTM_FP64 && n_mp >= kPipelinedMps) {
     launch_lme_pipelined(n_nodes, x_nodes, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
@@ -591,17 +637,27 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
       kernel<<<kLmeAsmBlocks, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity,
                                            beta, tol, max_iter, lam, N, dn, diag, *fused, chunk);
     };
-    const bool heat = fused->heat != nullptr;
-    if (precision == OTM_FP64) {
-      if (heat) run(k_lme_asm<G, PPL, double, true, double>, (double*)dN);
-      else run(k_lme_asm<G, PPL, double, false, double>, (double*)dN);
-    } else if (precision == OTM_MIXED) {
-      if (heat) run(k_lme_asm<G, PPL, float, true, float>, (float*)dN);
-      else run(k_lme_asm<G, PPL, float, false, float>, (float*)dN);
-    } else {
-      if (heat) run(k_lme_asm<G, PPL, float, true, double>, (float*)dN);
-      else run(k_lme_asm<G, PPL, float, false, double>, (float*)dN);
-    }
+    auto pick = [&](auto leave) {
+      constexpr bool LEAVE = decltype(leave)::value;
+      const bool heat = fused->heat != nullptr;
+      if (precision == OTM_FP64) {
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, double, true, double>, (double*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, double, false, double>, (double*)dN);
+      } else if (precision == OTM_MIXED) {
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, float>, (float*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, float, false, float>, (float*)dN);
+      } else {
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, double>, (float*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, float, false, double>, (float*)dN);
+      }
+    };
+    // Lists kept over steps carry a skin, and with it many rows past G * PPL
+    // pairs (one in ten at 0.1 h: nearly every wave has one), which are then
+    // left to the packed pass: 0.55M MPs 381 us, 535 in place.  Lists of the
+    // step's own radius have next to none, and the code that leaves them costs
+    // the other rows 1.4 % (1.13M MPs 646 us, 637 in place).
+    if (kept) pick(std::true_type{});
+    else pick(std::false_type{});
     return;
   }
   const unsigned nb = (unsigned)((n_mp + (256 / G) - 1) / (256 / G));

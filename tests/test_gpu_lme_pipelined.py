@@ -95,6 +95,34 @@ def test_float32_values_do_not_depend_on_the_size(precision, radius):
         assert torch.equal(torch.nan_to_num(big), torch.nan_to_num(small))
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed", "mixed_storage"])
+@pytest.mark.parametrize("over", [{}, {"kappa": 400.0}])
+@pytest.mark.parametrize("skin_h", [0.0, 0.15, 0.3])
+def test_kept_lists_give_the_values_of_new_ones(precision, over, skin_h):
+    """Rows past 36 pairs are solved in their round after a search and packed
+    together with kept lists: the same bits, whatever their share of the rows."""
+    w = W.taylor_rod(h=3.2e-3 / 5.8, seed=2, length=16e-3, skin_h=skin_h)
+    sim, p = make_sim(w, precision=precision, **over)
+    sim.init()
+    sim.run(2)
+    lam = sim.lam.clone()
+    sim.refresh(rebuild=True)
+    P = int(sim.offsets[-1])
+    rows = torch.diff(sim.offsets)
+    assert skin_h == 0.0 or float((rows > 36).double().mean()) > 0.05
+    want = [t.clone() for t in (sim.lam, sim.N[:P], sim.dN[:, :P])]
+    sums = [sim.m.clone(), sim.f.clone()]
+    sim.N[:P] = -1.0
+    sim.dN[:, :P] = -1.0
+    sim.lam.copy_(lam)
+    sim.refresh(rebuild=False)
+    for a, b in zip((sim.lam, sim.N[:P], sim.dN[:, :P]), want):
+        assert torch.equal(a, b)
+    # the sums' order is free: a few hundred terms each
+    assert float((sim.m - sums[0]).abs().max()) <= 1e-13 * float(sums[0].max())
+    assert float((sim.f - sums[1]).abs().max()) <= 1e-12 * float(sums[1].abs().max())
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed_storage"])
 @pytest.mark.parametrize("over", [{}, {"kappa": 400.0}])
 @pytest.mark.parametrize("skin_h,order", [(0.0, "morton"), (0.15, "lattice")])
