@@ -218,7 +218,7 @@ static void refresh_impl(otm_state& st, const otm_params& p, bool rebuild, int32
   } else {
     mark(ev, 4, s);
     if (mode == OTM_SCATTER_ATOMIC) {
-      if (!fuse_atomic) launch_assemble_atomic(st, sb, s);
+      if (stab) launch_assemble_atomic(st, sb, s);
     } else {
       if (rebuild || tr) launch_influence_lists(st, w, s);
       mark(ev, 5, s);

@@ -423,12 +423,6 @@ OTM_DEV int32_t table_probe(NodeTableV<V>& t, int32_t I, int32_t h) {
   return -1;
 }
 
-OTM_DEV void table_insert(NodeTable& t, int32_t I, double c0, double c1, double c2, double c3,
-                          double* m, double* f, int64_t n_nodes) {
-  const double c[4] = {c0, c1, c2, c3};
-  table_insert<4>(t, I, c, mf_dst(m, f, n_nodes));
-}
-
 // Every lane of the workgroup calls this after a barrier; it ends cleared
 // (a barrier is needed before the next inserts).
 template <int V>

@@ -269,7 +269,7 @@ void launch_influence_lists(const otm_state& st, const Workspace& w, hipStream_t
 constexpr int kScLanes = 8;
 constexpr int kScMPs = 256 / kScLanes;
 
-template <typename R, typename Q, bool STAB>
+template <typename R, typename Q>
 __global__ __launch_bounds__(256) void k_seg_contrib(
     int64_t n_mp, int64_t cap, const int64_t* __restrict__ offsets,
     const int32_t* __restrict__ idx, const double* __restrict__ N, const R* __restrict__ dN,
@@ -285,13 +285,13 @@ __global__ __launch_bounds__(256) void k_seg_contrib(
   const R s0 = sigma[p], s1 = sigma[n_mp + p], s2 = sigma[2 * n_mp + p];
   const R s3 = sigma[3 * n_mp + p], s4 = sigma[4 * n_mp + p], s5 = sigma[5 * n_mp + p];
   StabMP sm;
-  if constexpr (STAB) stab_load(sb, n_mp, p, sm);
+  stab_load(sb, n_mp, p, sm);
   for (int64_t q = offsets[p] + lane; q < offsets[p + 1]; q += kScLanes) {
     const R g0 = dN[q], g1 = dN[cap + q], g2 = dN[2 * cap + q];
     const double Nq = N[q];
     double c1, c2, c3;
     pair_force<Q>(v, s0, s1, s2, s3, s4, s5, g0, g1, g2, c1, c2, c3);
-    if constexpr (STAB) stab_add(sb, sm, idx[q], Nq, c1, c2, c3);
+    stab_add(sb, sm, idx[q], Nq, c1, c2, c3);
     contrib[pos_of[q]] = make_double4(Nq * mp, c1, c2, c3);
   }
 }
@@ -325,13 +325,13 @@ __global__ __launch_bounds__(256) void k_seg_gather(int64_t n_nodes, int64_t n_m
   }
 }
 
-template <typename R, typename Q, bool STAB>
+template <typename R, typename Q>
 static void seg_contrib(const otm_state& st, const Workspace& w, const Stab& sb, hipStream_t s) {
   const int64_t nm = st.n_mp;
   const unsigned nb = (unsigned)((nm + kScMPs - 1) / kScMPs);
-  k_seg_contrib<R, Q, STAB><<<nb, 256, 0, s>>>(nm, st.pair_capacity, st.nbr_offsets, st.nbr_idx,
-                                            st.N, (const R*)st.dN, st.vol, st.mass,
-                                            (const R*)st.sigma, w.tr_pos, w.contrib, sb);
+  k_seg_contrib<R, Q><<<nb, 256, 0, s>>>(nm, st.pair_capacity, st.nbr_offsets, st.nbr_idx, st.N,
+                                        (const R*)st.dN, st.vol, st.mass, (const R*)st.sigma,
+                                        w.tr_pos, w.contrib, sb);
 }
 
 void launch_scatter_segmented(const otm_state& st, const Workspace& w, const Stab& sb,
@@ -339,16 +339,9 @@ void launch_scatter_segmented(const otm_state& st, const Workspace& w, const Sta
   const int64_t nn = st.n_nodes, nm = st.n_mp;
   if (nn <= 0) return;
   if (nm > 0) {
-    const bool stab = sb.eps > 0.0;
-    if (st.precision == OTM_FP64)
-      stab ? seg_contrib<double, double, true>(st, w, sb, s)
-           : seg_contrib<double, double, false>(st, w, sb, s);
-    else if (st.precision == OTM_MIXED)
-      stab ? seg_contrib<float, float, true>(st, w, sb, s)
-           : seg_contrib<float, float, false>(st, w, sb, s);
-    else
-      stab ? seg_contrib<float, double, true>(st, w, sb, s)
-           : seg_contrib<float, double, false>(st, w, sb, s);
+    if (st.precision == OTM_FP64) seg_contrib<double, double>(st, w, sb, s);
+    else if (st.precision == OTM_MIXED) seg_contrib<float, float>(st, w, sb, s);
+    else seg_contrib<float, double>(st, w, sb, s);
   }
   launch_seg_gather(st, w, s);
 }
@@ -365,97 +358,92 @@ void launch_seg_gather(const otm_state& st, const Workspace& w, hipStream_t s) {
 
 namespace otm {
 
-// Atomic assembly with workgroup pre-aggregation.  A workgroup takes 512
-// consecutive MPs (spatially compact, so they share most of their nodes),
-// sums their contributions per node in an LDS table (NodeTable), then adds
-// each distinct node's four sums to m and f with one float64 atomic each.
-// Summation order varies from run to run.  Without the stabilisation term
-// the step fuses this into the shape-function kernel instead (lme.hip).
+// Atomic assembly of the stabilised residual (without that term the
+// shape-function kernels assemble), with workgroup pre-aggregation.  A
+// workgroup takes up to 512 consecutive MPs (spatially compact, so they share
+// most of their nodes), sums their contributions per node in an LDS table
+// (NodeTable), then adds each distinct node's four sums to m and f with one
+// float64 atomic each.  Summation order varies from run to run.
+//
+// Bound by the latency of a round's chain (row bounds, ids, node records, table
+// slots), so by the waves in flight: four workgroups per CU, with two of a
+// lane's pairs under way at a time.  268k MPs 144 us; with four pairs at a time,
+// two workgroups per CU and 512 MPs in each (524 workgroups on 512 places) 190.
 constexpr int kAsmMPs = 512;
 constexpr int kAsmLanes = 8;
+constexpr int kAsmRound = 256 / kAsmLanes;  // MPs
+constexpr int kAsmBlocks = 4 * 256;
 
-template <typename R, typename Q, bool STAB>
-__global__ __launch_bounds__(256) void k_assemble_atomic(
+template <typename R, typename Q>
+__global__ __launch_bounds__(256, 4) void k_assemble_atomic(
     int64_t n_nodes, int64_t n_mp, int64_t cap, const int64_t* __restrict__ offsets,
     const int32_t* __restrict__ idx, const double* __restrict__ N, const R* __restrict__ dN,
     const double* __restrict__ vol, const double* __restrict__ mass, const R* __restrict__ sigma,
-    double* __restrict__ m, double* __restrict__ f, Stab sb) {
+    double* __restrict__ m, double* __restrict__ f, Stab sb, int chunk) {
   __shared__ NodeTable table;
   const int tid = threadIdx.x;
   table_clear(table, tid, 256);
   __syncthreads();
   const bool ok = offsets[n_mp] <= cap;
-  const int64_t base = (int64_t)xcd_block() * kAsmMPs;
+  const int64_t base = (int64_t)xcd_block() * chunk;
   const int lane = tid % kAsmLanes;
-  for (int r = 0; r < kAsmMPs / (256 / kAsmLanes); ++r) {
-    const int64_t p = base + r * (256 / kAsmLanes) + tid / kAsmLanes;
-    if (!ok || p >= n_mp) continue;
+  const NodeDst<4> dst = mf_dst(m, f, n_nodes);
+  for (int r = 0; r < chunk; r += kAsmRound) {
+    const int64_t p = base + r + tid / kAsmLanes;
+    if (!ok || p >= n_mp || r + tid / kAsmLanes >= chunk) continue;
+    const int64_t o0 = offsets[p];
+    const int K = (int)(offsets[p + 1] - o0);
+    if (K == 0) continue;
     const double mp = mass[p];
     const double v = vol[p];
     const R s0 = sigma[p], s1 = sigma[n_mp + p], s2 = sigma[2 * n_mp + p];
     const R s3 = sigma[3 * n_mp + p], s4 = sigma[4 * n_mp + p], s5 = sigma[5 * n_mp + p];
-    const int64_t o0 = offsets[p], o1 = offsets[p + 1];
-    if (o1 == o0) continue;
     StabMP sm;
-    if constexpr (STAB) stab_load(sb, n_mp, p, sm);
-    auto insert = [&](int32_t I, double c0, double c1, double c2, double c3) {
-      table_insert(table, I, c0, c1, c2, c3, m, f, n_nodes);
-    };
-    auto contrib = [&](int64_t q, int32_t& I, double& c0, double& c1, double& c2, double& c3) {
-      I = idx[q];
-      const R g0 = dN[q], g1 = dN[cap + q], g2 = dN[2 * cap + q];
-      const double Nq = N[q];
-      c0 = Nq * mp;
-      pair_force<Q>(v, s0, s1, s2, s3, s4, s5, g0, g1, g2, c1, c2, c3);
-      if constexpr (STAB) stab_add(sb, sm, I, Nq, c1, c2, c3);
-    };
-    const int K = (int)(o1 - o0);
-    auto slot = [&](int t) { return o0 + t; };
-    // first 4 slots per lane: loads issued together (row start stands in for
-    // slots past the end), then the table updates
-    int32_t Iu[4];
-    double cu[4][4];
+    stab_load(sb, n_mp, p, sm);
+    for (int t0 = 0; t0 < K; t0 += 2 * kAsmLanes) {
+      // both pairs' loads together (the row's first pair stands in for a slot
+      // past its end), then the table updates
+      int32_t I[2];
+      bool use[2];
+      double c[2][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int t = k * kAsmLanes + lane;
-      contrib(t < K ? slot(t) : o0, Iu[k], cu[k][0], cu[k][1], cu[k][2], cu[k][3]);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k * kAsmLanes + lane < K) insert(Iu[k], cu[k][0], cu[k][1], cu[k][2], cu[k][3]);
-    for (int t = 4 * kAsmLanes + lane; t < K; t += kAsmLanes) {
-      int32_t I;
-      double c0, c1, c2, c3;
-      contrib(slot(t), I, c0, c1, c2, c3);
-      insert(I, c0, c1, c2, c3);
+      for (int k = 0; k < 2; ++k) {
+        const int t = t0 + k * kAsmLanes + lane;
+        use[k] = t < K;
+        const int64_t q = use[k] ? o0 + t : o0;
+        I[k] = idx[q];
+        const R g0 = dN[q], g1 = dN[cap + q], g2 = dN[2 * cap + q];
+        const double Nq = N[q];
+        c[k][0] = Nq * mp;
+        pair_force<Q>(v, s0, s1, s2, s3, s4, s5, g0, g1, g2, c[k][1], c[k][2], c[k][3]);
+        stab_add(sb, sm, I[k], Nq, c[k][1], c[k][2], c[k][3]);
+      }
+      table_insert_batch<4, 2>(table, I, use, c, dst);
     }
   }
   __syncthreads();
   table_flush(table, tid, 256, m, f, n_nodes);
 }
 
-template <typename R, typename Q, bool STAB>
+template <typename R, typename Q>
 static void assemble_atomic(const otm_state& st, const Stab& sb, hipStream_t s) {
+  // every workgroup that fits busy, with up to kAsmMPs MPs each: 512 apiece
+  // would leave a body of 0.27M MPs at 524 workgroups for 1024 places
   const int64_t nm = st.n_mp;
-  const unsigned nb = (unsigned)((nm + kAsmMPs - 1) / kAsmMPs);
-  k_assemble_atomic<R, Q, STAB><<<nb, 256, 0, s>>>(st.n_nodes, nm, st.pair_capacity,
-                                                st.nbr_offsets, st.nbr_idx, st.N,
-                                                (const R*)st.dN, st.vol, st.mass,
-                                                (const R*)st.sigma, st.m, st.f, sb);
+  int64_t chunk = (nm + kAsmBlocks - 1) / kAsmBlocks;
+  chunk = (chunk + kAsmRound - 1) / kAsmRound * kAsmRound;
+  if (chunk > kAsmMPs) chunk = kAsmMPs;
+  const unsigned nb = (unsigned)((nm + chunk - 1) / chunk);
+  k_assemble_atomic<R, Q><<<nb, 256, 0, s>>>(st.n_nodes, nm, st.pair_capacity, st.nbr_offsets,
+                                             st.nbr_idx, st.N, (const R*)st.dN, st.vol, st.mass,
+                                             (const R*)st.sigma, st.m, st.f, sb, (int)chunk);
 }
 
 void launch_assemble_atomic(const otm_state& st, const Stab& sb, hipStream_t s) {
   if (st.n_mp <= 0) return;
-  const bool stab = sb.eps > 0.0;
-  if (st.precision == OTM_FP64)
-    stab ? assemble_atomic<double, double, true>(st, sb, s)
-         : assemble_atomic<double, double, false>(st, sb, s);
-  else if (st.precision == OTM_MIXED)
-    stab ? assemble_atomic<float, float, true>(st, sb, s)
-         : assemble_atomic<float, float, false>(st, sb, s);
-  else
-    stab ? assemble_atomic<float, double, true>(st, sb, s)
-         : assemble_atomic<float, double, false>(st, sb, s);
+  if (st.precision == OTM_FP64) assemble_atomic<double, double>(st, sb, s);
+  else if (st.precision == OTM_MIXED) assemble_atomic<float, float>(st, sb, s);
+  else assemble_atomic<float, double>(st, sb, s);
 }
 
 }  // namespace otm
