@@ -187,7 +187,7 @@ static void refresh_impl(otm_state& st, const otm_params& p, bool rebuild, int32
   if (!packed) launch_pack_nodes(st, w.nodes, s);
   if (rebuild)
     launch_search(st.n_nodes, st.x, st.n_mp, st.xp, p.r_list, p.cell_size, st.pair_capacity,
-                  st.nbr_offsets, st.nbr_idx, w, diag, s);
+                  st.nbr_offsets, st.nbr_idx, w, diag, s, packed && node_update_boxes(st.n_nodes));
   mark(ev, 3, s);
   // Without the stabilisation term the assembly's per-pair work runs inside
   // the shape-function kernel, on N and grad N while they are in registers:
@@ -382,7 +382,8 @@ static otm_status step_impl(otm_state* st, const otm_params* p, double dt, int32
   if (check_workspace(ws, ws_bytes, st->n_nodes, st->n_mp, st->pair_capacity, &w) != OTM_OK)
     return OTM_ERR_ARG;
   mark(ev, 0, s);
-  launch_node_update(*st, *p, dt, scatter_mode == OTM_SCATTER_ATOMIC, w.nodes, diag, s);
+  launch_node_update(*st, *p, dt, scatter_mode == OTM_SCATTER_ATOMIC, w.nodes, diag, s,
+                     rebuild != 0 && node_update_boxes(st->n_nodes) ? &w : nullptr);
   mark(ev, 1, s);
   launch_mp_update(*st, *p, dt, w.nodes, diag, s);
   mark(ev, 2, s);

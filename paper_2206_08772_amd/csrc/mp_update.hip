@@ -22,6 +22,7 @@
 
 #include <type_traits>
 
+#include "boxes.h"
 #include "constitutive.h"
 #include "launch.h"
 #include "otm_common.h"
@@ -110,58 +111,71 @@ __global__ __launch_bounds__(256) void k_node_update(int64_t n, double* __restri
                                                      double4* __restrict__ packed,
                                                      int64_t n_mp, otm_diag* diag,
                                                      ToolArgs tool, double* __restrict__ heat,
-                                                     double cp) {
+                                                     double cp, Box* boxes, BinCounters z) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double mi = m[i];
-  // conduction: the nodal temperature h_I / m_I and its rate Q_I / (Cp m_I)
-  // from the sums of the last assembly (0 at a node without mass)
-  double Ti = 0.0, Ri = 0.0;
-  if (heat != nullptr && mi > 0.0) {
-    Ti = heat[i] / mi;
-    Ri = heat[n + i] / (cp * mi);
-  }
-  double u[3], xs[3], xo[3], fi[3];
+  Box b;
+  b.clear();
+  if (i < n) {
+    const double mi = m[i];
+    // conduction: the nodal temperature h_I / m_I and its rate Q_I / (Cp m_I)
+    // from the sums of the last assembly (0 at a node without mass)
+    double Ti = 0.0, Ri = 0.0;
+    if (heat != nullptr && mi > 0.0) {
+      Ti = heat[i] / mi;
+      Ri = heat[n + i] / (cp * mi);
+    }
+    double u[3], xs[3], xo[3], fi[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    xo[c] = x[c * n + i];
-    u[c] = du[c * n + i];
-    fi[c] = f[c * n + i];
-  }
-  if (tool.on) {
-    double fc[3];
-    tool_contact(tool, n, i, xo, u, mi, fc);
+    for (int c = 0; c < 3; ++c) {
+      xo[c] = x[c * n + i];
+      u[c] = du[c * n + i];
+      fi[c] = f[c * n + i];
+    }
+    if (tool.on) {
+      double fc[3];
+      tool_contact(tool, n, i, xo, u, mi, fc);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) fi[c] += fc[c];
-  }
+      for (int c = 0; c < 3; ++c) fi[c] += fc[c];
+    }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    // a node outside every support (no mass, no force) keeps its increment
-    u[c] = u[c] + (mi > 0.0 ? dt2 * fi[c] / mi : 0.0);
-    xs[c] = xo[c] + u[c];
-  }
-  if (wall) {
-    const double g = (xs[0] - wx0) * wn0 + (xs[1] - wx1) * wn1 + (xs[2] - wx2) * wn2;
-    if (g < 0.0) {
-      xs[0] -= g * wn0; xs[1] -= g * wn1; xs[2] -= g * wn2;
+    for (int c = 0; c < 3; ++c) {
+      // a node outside every support (no mass, no force) keeps its increment
+      u[c] = u[c] + (mi > 0.0 ? dt2 * fi[c] / mi : 0.0);
+      xs[c] = xo[c] + u[c];
+    }
+    if (wall) {
+      const double g = (xs[0] - wx0) * wn0 + (xs[1] - wx1) * wn1 + (xs[2] - wx2) * wn2;
+      if (g < 0.0) {
+        xs[0] -= g * wn0; xs[1] -= g * wn1; xs[2] -= g * wn2;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) u[c] = xs[c] - xo[c];
+        for (int c = 0; c < 3; ++c) u[c] = xs[c] - xo[c];
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[c * n + i] = xs[c];
+      du[c * n + i] = u[c];
+    }
+    if (!(isfinite(xs[0]) && isfinite(xs[1]) && isfinite(xs[2])))
+      diag_fail(diag, OTM_ERR_NONFINITE, (uint64_t)(n_mp + i));
+    if (zero_mf) {
+      m[i] = 0.0;
+      f[i] = 0.0; f[n + i] = 0.0; f[2 * n + i] = 0.0;
+      if (heat != nullptr) { heat[i] = 0.0; heat[n + i] = 0.0; }
+    }
+    packed[2 * i] = make_double4(xs[0], xs[1], xs[2], u[0]);
+    packed[2 * i + 1] = make_double4(u[1], u[2], Ti, Ri);
+    if (boxes != nullptr) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) b.add(c, xs[c]);
     }
   }
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    x[c * n + i] = xs[c];
-    du[c * n + i] = u[c];
-  }
-  if (!(isfinite(xs[0]) && isfinite(xs[1]) && isfinite(xs[2])))
-    diag_fail(diag, OTM_ERR_NONFINITE, (uint64_t)(n_mp + i));
-  if (zero_mf) {
-    m[i] = 0.0;
-    f[i] = 0.0; f[n + i] = 0.0; f[2 * n + i] = 0.0;
-    if (heat != nullptr) { heat[i] = 0.0; heat[n + i] = 0.0; }
-  }
-  packed[2 * i] = make_double4(xs[0], xs[1], xs[2], u[0]);
-  packed[2 * i + 1] = make_double4(u[1], u[2], Ti, Ri);
+  if (boxes == nullptr) return;
+  // the box of the workgroup's nodes and the cleared counters, for the search
+  __shared__ Box sh[4];
+  z.clear();
+  b.block_join(sh);
+  if (threadIdx.x == 0) boxes[blockIdx.x] = b;
 }
 
 __global__ __launch_bounds__(256) void k_pack_nodes(int64_t n, const double* __restrict__ x,
@@ -180,7 +194,8 @@ void launch_pack_nodes(const otm_state& st, double4* packed, hipStream_t s) {
 }
 
 void launch_node_update(const otm_state& st, const otm_params& p, double dt, bool zero_mf,
-                        double4* packed, otm_diag* diag, hipStream_t s) {
+                        double4* packed, otm_diag* diag, hipStream_t s,
+                        const Workspace* boxes) {
   const int64_t n = st.n_nodes;
   if (n <= 0) return;
   ToolArgs t{};
@@ -199,7 +214,9 @@ void launch_node_update(const otm_state& st, const otm_params& p, double dt, boo
   k_node_update<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(
       n, st.x, st.du, st.m, st.f, dt * dt, p.wall_enabled, p.wall_x[0], p.wall_x[1],
       p.wall_x[2], p.wall_n[0], p.wall_n[1], p.wall_n[2], zero_mf ? 1 : 0, packed, st.n_mp,
-      diag, t, p.kappa > 0.0 ? st.heat : nullptr, p.Cp);
+      diag, t, p.kappa > 0.0 ? st.heat : nullptr, p.Cp,
+      boxes != nullptr ? reinterpret_cast<Box*>(boxes->bbox_part) : nullptr,
+      boxes != nullptr ? bin_counters(*boxes) : BinCounters{});
 }
 
 // ----------------------------------------------------- material-point pass

@@ -13,10 +13,12 @@
 // hundred words they read and reduce themselves: the grid from the box
 // partials (in the count), the totals before a scan workgroup, the pairs
 // before a compaction group.  6 launches up to 8192 MPs and 16384 cells, 7 to 8
-// above, where up to 13 were needed.  Search of 4096 MPs: 32 us of kernel time,
+// above, where up to 13 were needed; a step of up to 65536 nodes spares the box
+// launch too (the node update forms the partials).  Search of 4096 MPs: 32 us of kernel time,
 // 73 before; 27.6k: 47 (86); 108k: 77 (99); 1.13M: 301 (352).
 #include <type_traits>
 
+#include "boxes.h"
 #include "launch.h"
 #include "otm_common.h"
 
@@ -191,48 +193,6 @@ __global__ void k_diag_reset(otm_diag* d) {
 void launch_diag_reset(otm_diag* d, hipStream_t s) { k_diag_reset<<<1, 1, 0, s>>>(d); }
 
 // ---------------------------------------------------------------- cell grid
-// Bounding box partials of the nodes, one per workgroup; the same launch clears
-// the cell counters of the node and MP binnings that follow.
-struct BinCounters {
-  int32_t* node_start;  // [cap + 1]
-  int32_t* mp_start;    // [cap + 1]
-  int64_t cap;
-  int32_t* ticket;      // of the pair runs' workgroups
-};
-
-struct Box {
-  double lo[3], hi[3];
-  OTM_DEV void clear() {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      lo[c] = INFINITY;
-      hi[c] = -INFINITY;
-    }
-  }
-  OTM_DEV void wave_join() {
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        lo[c] = fmin(lo[c], __shfl_xor(lo[c], o));
-        hi[c] = fmax(hi[c], __shfl_xor(hi[c], o));
-      }
-    }
-  }
-  // Over a workgroup of 256 threads, in every thread (sh: 4 boxes).
-  OTM_DEV void block_join(Box* sh) {
-    wave_join();
-    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = *this;
-    __syncthreads();
-    for (int w = 0; w < 4; ++w) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        lo[c] = fmin(lo[c], sh[w].lo[c]);
-        hi[c] = fmax(hi[c], sh[w].hi[c]);
-      }
-    }
-  }
-};
-
 // Nodes per bounding-box workgroup: four per thread, more past kBBoxBlocks
 // workgroups (every counting workgroup reads all their boxes).
 static unsigned bbox_blocks(int64_t n) {
@@ -240,25 +200,18 @@ static unsigned bbox_blocks(int64_t n) {
   return (unsigned)(b < 1 ? 1 : (b < kBBoxBlocks ? b : kBBoxBlocks));
 }
 
+// Bounding box partials of the nodes, one per workgroup; the same launch clears
+// the cell counters of the node and MP binnings that follow.
 __global__ __launch_bounds__(256) void k_bbox_partial(const double* x, int64_t n, Box* part,
                                                       BinCounters z) {
   __shared__ Box sh[4];
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= z.cap;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    z.node_start[i] = 0;
-    z.mp_start[i] = 0;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *z.ticket = 0;
+  z.clear();
   Box b;
   b.clear();
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const double v = x[c * n + i];
-      b.lo[c] = fmin(b.lo[c], v);
-      b.hi[c] = fmax(b.hi[c], v);
-    }
+    for (int c = 0; c < 3; ++c) b.add(c, x[c * n + i]);
   }
   b.block_join(sh);
   if (threadIdx.x == 0) part[blockIdx.x] = b;
@@ -969,15 +922,18 @@ __global__ void k_search_empty(int64_t* offsets, otm_diag* diag) {
 
 void launch_search(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
                    double r_list, double cell_size, int64_t pair_capacity, int64_t* nbr_offsets,
-                   int32_t* nbr_idx, const Workspace& w, otm_diag* diag, hipStream_t s) {
+                   int32_t* nbr_idx, const Workspace& w, otm_diag* diag, hipStream_t s,
+                   bool boxed) {
   if (n_mp <= 0) {
     k_search_empty<<<1, 1, 0, s>>>(nbr_offsets, diag);
     return;
   }
-  const BinCounters z{w.cell_start, w.mp_cell_start, w.cap_cells, w.ticket};
   Box* part = reinterpret_cast<Box*>(w.bbox_part);
-  const unsigned n_part = bbox_blocks(n_nodes);
-  k_bbox_partial<<<n_part, 256, 0, s>>>(x_nodes, n_nodes, part, z);
+  unsigned n_part = (unsigned)((n_nodes + 255) / 256);
+  if (!boxed) {
+    n_part = bbox_blocks(n_nodes);
+    k_bbox_partial<<<n_part, 256, 0, s>>>(x_nodes, n_nodes, part, bin_counters(w));
+  }
   // nodes and MPs binned on the grid together: one count, one two-array scan,
   // one fill.  The MPs' ranks lie where their rows are staged later.
   const BinSet nodes{x_nodes, n_nodes, w.node_cell, w.node_rank, w.cell_start, w.sorted};
