@@ -424,7 +424,7 @@ OTM_DEV void mp_adjoint(const AdjMpArgs& a, int64_t p, const double dF[3][3], do
       dtr.v[k] = h.a[i][j] + h.a[j][i] +
                  (h.a[i][0] * h.a[j][0] + h.a[i][1] * h.a[j][1] + h.a[i][2] * h.a[j][2]) + hbh;
     }
-    jacobi_eig(dtr, d, V);
+    jacobi_eig<true>(dtr, d, V);
   }
   for (int k = 0; k < 3; ++k) e[k] = 0.5 * log1p(d[k]);
   tr = e[0] + e[1] + e[2];

@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
                  (h.a[i][0] * h.a[j][0] + h.a[i][1] * h.a[j][1] + h.a[i][2] * h.a[j][2]) + hbh;
     }
     Q d[3], V[3][3];
-    jacobi_eig(dtr, d, V);
+    jacobi_eig<std::is_same_v<R, double>>(dtr, d, V);
     Q e[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) e[a] = Q(0.5) * m_log1p(d[a]);

@@ -231,10 +231,39 @@ OTM_HD M3<R> full(const S3<R>& s) {
   return A;
 }
 
+// 1 / sqrt(x) of a normal x > 0 to about an ulp: the hardware's estimate (2^-24)
+// and one third-order step.
+OTM_DEV double rsqrt_refined(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// The rotation that annihilates apq: t = tan, c = cos, sn = sin of the smaller
+// angle.  Without divisions and square roots, which were two thirds of a
+// sweep's instructions: with a = aqq - app, b = 2 apq and y = 1 / sqrt(a^2 + b^2),
+// cos 2phi = |a| y, c^2 = (1 + cos 2phi) / 2 and sn = b y / (2 c) (the sign of a).
+OTM_DEV void jacobi_angle_fp64(double app, double aqq, double apq, double& t, double& c,
+                               double& sn) {
+  double a = aqq - app, b = 2.0 * apq;
+  if (fabs(a) + fabs(b) < 1e-140) {  // the squares would underflow
+    a *= 0x1p500;
+    b *= 0x1p500;
+  }
+  const double y = rsqrt_refined(fma(a, a, b * b));
+  const double c2 = fma(0.5 * fabs(a), y, 0.5);
+  const double rc = rsqrt_refined(c2);
+  c = c2 * rc;
+  sn = 0.5 * (a < 0.0 ? -b : b) * y * rc;
+  t = sn * rc;
+}
+
 // Eigen-decomposition of a symmetric 3x3 by cyclic Jacobi rotations:
 // on return d[k] are the eigenvalues and column k of V the eigenvectors.
-template <typename R>
-OTM_HD void jacobi_eig(const S3<R>& s, R d[3], R V[3][3]) {
+// FP64: with the rotation angles of jacobi_angle_fp64 (another last bit, so
+// not where results are stored in float32).
+template <bool FP64, typename R>
+OTM_DEV void jacobi_eig(const S3<R>& s, R d[3], R V[3][3]) {
   R a00 = s.v[0], a11 = s.v[1], a22 = s.v[2];
   R a01 = s.v[3], a12 = s.v[4], a02 = s.v[5];
 #pragma unroll
@@ -254,10 +283,15 @@ OTM_HD void jacobi_eig(const S3<R>& s, R d[3], R V[3][3]) {
       else if (plane == 1) { app = a00; aqq = a22; apq = a02; }
       else { app = a11; aqq = a22; apq = a12; }
       if (fabs(apq) < tiny) continue;
-      const R theta = (aqq - app) / (R(2) * apq);
-      const R t = (theta >= R(0) ? R(1) : R(-1)) / (fabs(theta) + sqrt(theta * theta + R(1)));
-      const R c = R(1) / sqrt(t * t + R(1));
-      const R sn = t * c;
+      R t, c, sn;
+      if constexpr (FP64) {
+        jacobi_angle_fp64(app, aqq, apq, t, c, sn);
+      } else {
+        const R theta = (aqq - app) / (R(2) * apq);
+        t = (theta >= R(0) ? R(1) : R(-1)) / (fabs(theta) + sqrt(theta * theta + R(1)));
+        c = R(1) / sqrt(t * t + R(1));
+        sn = t * c;
+      }
       const R np = app - t * apq, nq = aqq + t * apq;
       if (plane == 0) {
         const R r02 = c * a02 - sn * a12, r12 = sn * a02 + c * a12;
