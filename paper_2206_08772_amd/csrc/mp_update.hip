@@ -2,7 +2,7 @@
 // and the material-point pass: positions, incremental deformation gradient,
 // F, volume and the constitutive update.
 //
-// Material-point pass, one workgroup per 256 MPs:
+// Material-point pass, one workgroup per 256 MPs (fewer for small bodies):
 //   phase 1 (gather): groups of 16 lanes walk one MP's pairs with unit stride,
 //     accumulate x_p = sum N_I x_I and H = dF - 1 = sum du_I (x) grad N_I,
 //     reduce by shuffles and park the 12 sums in LDS;
@@ -233,8 +233,11 @@ constexpr int kSlots = 32 / kGather;   // pairs per lane loaded branch-free
 // index, so idx, N and each component of grad N come in one load of two
 // values (8 or 16 bytes) instead of two; this needs idx 8-byte, N and grad N
 // 2 sizeof(R)-byte aligned and an even capacity (the launcher checks).
-template <typename R, bool COND, typename Q = R, bool PAIRED = false>
-__global__ __launch_bounds__(kMpBlock) void k_mp_update(
+//
+// SMALL: `rounds` rounds of MPs per workgroup, otherwise kGather (a constant:
+// the pass needs 6 VGPRs more without, a workgroup per CU fewer in OTM_MIXED).
+template <typename R, bool COND, typename Q, bool PAIRED, bool SMALL>
+__global__ __launch_bounds__(kMpBlock, 4) void k_mp_update(
     const double4* __restrict__ nodes, int64_t n_nodes, int64_t n_mp,
     const int64_t* __restrict__ offsets, const int32_t* __restrict__ idx,
     int64_t cap, const double* __restrict__ N, const R* __restrict__ dN,
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
     double* __restrict__ epsbar, double* __restrict__ T, R* __restrict__ sigma, Mat<Q> M,
     double* __restrict__ xp_prev, double* __restrict__ dFm1, int32_t* __restrict__ failed,
     double* __restrict__ clock, double dt, otm_diag* diag, double kappa,
-    double* __restrict__ qflux) {
+    double* __restrict__ qflux, int small_rounds) {
   // phase 1: the 12 (16 with conduction) gathered sums of each MP; phase 2:
   // the MP's eigenvectors, logarithmic strains and J parked in sums[0..12]
   // over the return-map solve (each lane only touches its own column)
@@ -252,7 +255,9 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
   // sums of one MP hit different LDS banks
   __shared__ double sums[kSums][kMpBlock + 1];
   __shared__ int64_t row[kMpBlock + 1];
-  const int64_t base = (int64_t)xcd_block() * kMpBlock;
+  const int rounds = SMALL ? small_rounds : kGather;
+  const int block_mps = rounds * (kMpBlock / kGather);
+  const int64_t base = (int64_t)xcd_block() * block_mps;
   const int tid = threadIdx.x;
   // the tool's clock moves on here: the node update before has read it and
   // the next one comes after this kernel
@@ -260,11 +265,12 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
   const bool lists_ok = offsets[n_mp] <= cap;
   const bool have_nodes = n_nodes > 0 && cap > 0;
   // the block's row offsets, read once (rows past the end are empty)
-  for (int i = tid; i <= kMpBlock; i += kMpBlock) row[i] = offsets[min(base + i, n_mp)];
+  for (int i = tid; i <= block_mps; i += kMpBlock) row[i] = offsets[min(base + i, n_mp)];
   __syncthreads();
 
-  // phase 1: gather with kGather lanes per MP in kGather rounds of
-  // kMpBlock / kGather MPs, software-pipelined three deep.  Round r issues the
+  // phase 1: gather with kGather lanes per MP in `rounds` rounds (an even
+  // number, 4 to kGather) of kMpBlock / kGather MPs, software-pipelined three
+  // deep.  Round r issues the
   // node gathers of round r + 1, then sums round r, then issues the pair data
   // (N, grad N) of round r + 2 and the node ids of round r + 3.  Vector loads
   // complete in issue order, so a wait can only leave younger loads in flight;
@@ -398,7 +404,6 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
     load_pairs(p1, 1);
     __builtin_amdgcn_sched_barrier(0);
     load_ids(i0, 2);
-    static_assert(kGather % 2 == 0 && kGather >= 6, "rounds are taken in pairs");
     // rounds r, r + 1, fetching ahead up to round r + 4 (with_ids: the ids of
     // round r + 4 exist)
     auto two_rounds = [&](int r, bool with_ids) {
@@ -417,15 +422,15 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
       load_pairs(p1, r + 3);
       if (with_ids) load_ids(i0, r + 4);
     };
-    for (int r = 0; r < kGather - 4; r += 2) two_rounds(r, true);
-    two_rounds(kGather - 4, false);
+    for (int r = 0; r < rounds - 4; r += 2) two_rounds(r, true);
+    two_rounds(rounds - 4, false);
     // the last two rounds: nothing left to fetch ahead
     __builtin_amdgcn_sched_barrier(0);
     load_nodes(n1, i1);
     __builtin_amdgcn_sched_barrier(0);
-    sum_round(kGather - 2, n0, p0);
+    sum_round(rounds - 2, n0, p0);
     __builtin_amdgcn_sched_barrier(0);
-    sum_round(kGather - 1, n1, p1);
+    sum_round(rounds - 1, n1, p1);
     __builtin_amdgcn_sched_barrier(0);
     // long rows: the pairs past the slots, summed per group and added to the
     // row's sums by the group's lane 0; the round totals were written by
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int r = 0; r < kGather; ++r) {
+    for (int r = 0; r < rounds; ++r) {
       const int local = r * kPer + grp;
       const int64_t o0 = row[local], o1 = row[local + 1];
       const int64_t done = (PAIRED ? (o0 & ~(int64_t)1) : o0) + kSlots * kGather;
@@ -473,7 +478,7 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
   // latency overlaps the end of the gathers and the update waits for them
   // once instead of once per input as it reaches it
   const int64_t p = base + tid;
-  const bool mine = p < n_mp && lists_ok;
+  const bool mine = tid < block_mps && p < n_mp && lists_ok;
   double vol_n = 0.0, ebn = 0.0, Tn = 0.0;
   R fd_n[9], bd_n[6];
   if (mine) {
@@ -675,6 +680,18 @@ __global__ __launch_bounds__(kMpBlock) void k_mp_update(
   if (!finite) diag_fail(diag, OTM_ERR_NONFINITE, (uint64_t)p);
 }
 
+// Rounds of kMpBlock / kGather MPs per workgroup: even, 4 to kGather, and no
+// more than spread a body over the 256 CUs.  A small body's pass is the chain
+// of one workgroup's rounds (4374 MPs: 16 us with 18 workgroups of 16 rounds,
+// 9 with 69 of 4).  More workgroups than CUs gain nothing and leave phase 2's
+// waves without MPs (steps of 108k MPs: 221 us with 422 workgroups of 16
+// rounds, 249 with 844 of 8).
+static int mp_rounds(int64_t n_mp) {
+  constexpr int64_t per_round = 256 * (kMpBlock / kGather);  // MPs, one round on each CU
+  const int64_t even = (n_mp + 2 * per_round - 1) / (2 * per_round) * 2;
+  return (int)(even < 4 ? 4 : (even < kGather ? even : kGather));
+}
+
 void launch_mp_update(const otm_state& st, const otm_params& p, double dt,
                       const double4* packed, otm_diag* diag, hipStream_t s) {
   const int64_t n = st.n_mp;
@@ -682,7 +699,9 @@ void launch_mp_update(const otm_state& st, const otm_params& p, double dt,
     if (p.tool_enabled) k_clock_advance<<<1, 1, 0, s>>>(st.clock, dt);
     return;
   }
-  const unsigned nb = (unsigned)((n + kMpBlock - 1) / kMpBlock);
+  const int rounds = mp_rounds(n);
+  const int64_t block_mps = (int64_t)rounds * (kMpBlock / kGather);
+  const unsigned nb = (unsigned)((n + block_mps - 1) / block_mps);
   double* hist_x = p.eps_stab > 0.0 ? st.xp_prev : nullptr;
   double* hist_f = p.eps_stab > 0.0 ? st.dFm1 : nullptr;
   int32_t* frac = p.fracture ? st.failed : nullptr;
@@ -691,7 +710,7 @@ void launch_mp_update(const otm_state& st, const otm_params& p, double dt,
     kernel<<<nb, kMpBlock, 0, s>>>(packed, st.n_nodes, n, st.nbr_offsets, st.nbr_idx,
                                    st.pair_capacity, st.N, dn, st.xp, st.vol, fd, bd, st.epsbar,
                                    st.T, sg, mat, hist_x, hist_f, frac, clock, dt, diag, p.kappa,
-                                   st.qflux);
+                                   st.qflux, rounds);
   };
   // paired pair loads where the arrays allow them (see k_mp_update)
   const size_t dn_size = st.precision == OTM_FP64 ? sizeof(double) : sizeof(float);
@@ -701,13 +720,18 @@ void launch_mp_update(const otm_state& st, const otm_params& p, double dt,
   auto pick = [&](auto r_tag, auto q_tag, auto dn, auto fd, auto bd, auto sg, auto m) {
     using R = decltype(r_tag);
     using Q = decltype(q_tag);
-    if (cond) {
-      if (paired) run(k_mp_update<R, true, Q, true>, dn, fd, bd, sg, m);
-      else run(k_mp_update<R, true, Q, false>, dn, fd, bd, sg, m);
-    } else {
-      if (paired) run(k_mp_update<R, false, Q, true>, dn, fd, bd, sg, m);
-      else run(k_mp_update<R, false, Q, false>, dn, fd, bd, sg, m);
-    }
+    auto sized = [&](auto small) {
+      constexpr bool S = decltype(small)::value;
+      if (cond) {
+        if (paired) run(k_mp_update<R, true, Q, true, S>, dn, fd, bd, sg, m);
+        else run(k_mp_update<R, true, Q, false, S>, dn, fd, bd, sg, m);
+      } else {
+        if (paired) run(k_mp_update<R, false, Q, true, S>, dn, fd, bd, sg, m);
+        else run(k_mp_update<R, false, Q, false, S>, dn, fd, bd, sg, m);
+      }
+    };
+    if (rounds < kGather) sized(std::true_type{});
+    else sized(std::false_type{});
   };
   if (st.precision == OTM_FP64) {
     pick(double{}, double{}, (const double*)st.dN, (double*)st.Fd, (double*)st.bed,
