@@ -581,12 +581,12 @@ def main():
     phases["mp_update"] = dict(roof, ms=round(ph["mp_update"], 4))
     # `roofline` is the MP pass (the kernel the HBM target is set on); the
     # longest kernel is the shape functions with the fused assembly
-    longest = dict(kernel="k_lme_asm<double> (LME Newton + fused atomic assembly)",
+    longest = dict(kernel="k_lme (float64 LME Newton + fused atomic assembly)",
                    ms=phases["lme_assembly"]["ms"],
                    share_of_step=round(phases["lme_assembly"]["ms"] / main_run["ms_per_step"], 3),
                    hbm_frac=phases["lme_assembly"]["frac"],
-                   bound="latency of the per-MP Newton chain at two waves per SIMD; FP64 VALU "
-                         "issue ~15 % of peak (profiles/valu_taylor_rod_fp64_mixed.md)")
+                   bound="arithmetic for half of its time (VALU issue at 85 %), then the stores "
+                         "of N and grad N and the node sums")
 
     line = {
         "metric": "material-point steps/s (FP64 vs mixed, 1 GPU) + adjoint/forward time ratio",

@@ -62,7 +62,7 @@ void launch_search(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const d
                    bool boxed = false);
 // The node update of a step that rebuilds its lists also forms the search's box
 // partials (``boxed``), one per 256 nodes, up to as many as the workspace
-// holds: that spares a launch of 4 to 5 us (a step of 4096 MPs 78 us, 82 with
+// holds: that spares a launch of 4 to 5 us (a step of 4374 MPs 80 us, 82 with
 // it).  More partials would cost the counting workgroups, which all read
 // them, what a launch costs.
 inline bool node_update_boxes(int64_t n_nodes) {

@@ -12,7 +12,7 @@
 // Measured on the rod with 1.13M MPs, deforming, shape functions with the fused
 // assembly: 0.66 ms against 0.74 ms with lme.hip's kernel; with a list skin of
 // 0.1 h (33 pairs per MP, a tenth of the MPs past that kernel's 36) 0.69
-// against 1.05 ms.  Of the 0.66 ms the arithmetic alone takes 0.35 (VALU issue
+// against 1.05 ms with those rows solved in their round.  Of the 0.66 ms the arithmetic alone takes 0.35 (VALU issue
 // at 85 %), the stores 0.10 (0.29 there: 17M write requests instead of 44M), the
 // table sums 0.06, their flush to memory 0.06 and the table slots 0.05.
 //

