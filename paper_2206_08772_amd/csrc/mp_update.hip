@@ -223,6 +223,8 @@ void launch_node_update(const otm_state& st, const otm_params& p, double dt, boo
 constexpr int kMpBlock = 256;
 constexpr int kGather = 16;            // lanes per MP in the gather phase
 constexpr int kSlots = 32 / kGather;   // pairs per lane loaded branch-free
+constexpr int kTail = 8;               // pairs past them that phase 2 may add
+constexpr int kFewTails = 4;           // rows of a wave that do not go there
 
 // Conduction (COND): the gather also sums grad T_p = sum_I T_I grad N_Ip and
 // sum_I N_Ip rate_I from the node records' (T_I, rate_I), kept in sums[13..16]
@@ -255,6 +257,7 @@ __global__ __launch_bounds__(kMpBlock, 4) void k_mp_update(
   // sums of one MP hit different LDS banks
   __shared__ double sums[kSums][kMpBlock + 1];
   __shared__ int64_t row[kMpBlock + 1];
+  __shared__ bool tails[kMpBlock / kWave];  // the wave leaves its rows' tails to phase 2
   const int rounds = SMALL ? small_rounds : kGather;
   const int block_mps = rounds * (kMpBlock / kGather);
   const int64_t base = (int64_t)xcd_block() * block_mps;
@@ -434,15 +437,32 @@ __global__ __launch_bounds__(kMpBlock, 4) void k_mp_update(
     __builtin_amdgcn_sched_barrier(0);
     // long rows: the pairs past the slots, summed per group and added to the
     // row's sums by the group's lane 0; the round totals were written by
-    // other lanes of the same wave, so a wave-level fence comes first
+    // other lanes of the same wave, so a wave-level fence comes first.  A wave
+    // with more than kFewTails rows of 1 to kTail such pairs leaves these to
+    // phase 2, one lane per row: here each takes a round of its own (lists with
+    // a 0.1 h skin, half of the rows: 0.58 ms at 1.13M MPs, 0.48 there; a few
+    // rows cost less here than phase 2's chain of loads, and so do those of a
+    // small body, where the question alone costs 1.5 us of 96).
+    constexpr int kGroups = kWave / kGather;
+    const int64_t slots_end = kSlots * kGather;
+    bool many = false;
+    if constexpr (!SMALL) {
+      const int l = tid % kWave;
+      const int local = l / kGroups * kPer + tid / kWave * kGroups + l % kGroups;
+      const bool has = l / kGroups < rounds;
+      const int64_t a = row[has ? local : 0], b = row[has ? local + 1 : 0];
+      const int64_t past = b - ((PAIRED ? (a & ~(int64_t)1) : a) + slots_end);
+      many = __builtin_popcountll(__ballot(has && past > 0 && past <= kTail)) > kFewTails;
+      if (l == 0) tails[tid / kWave] = many;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     for (int r = 0; r < rounds; ++r) {
       const int local = r * kPer + grp;
       const int64_t o0 = row[local], o1 = row[local + 1];
-      const int64_t done = (PAIRED ? (o0 & ~(int64_t)1) : o0) + kSlots * kGather;
-      if (o1 <= done) continue;  // uniform within the group
+      const int64_t done = (PAIRED ? (o0 & ~(int64_t)1) : o0) + slots_end;
+      if (o1 <= done + (many ? kTail : 0)) continue;  // uniform within the group
       double a[kGathered] = {};
       for (int64_t q = done + lane; q < o1; q += kGather) {
         const int32_t J = idx[q];
@@ -494,6 +514,81 @@ __global__ __launch_bounds__(kMpBlock, 4) void k_mp_update(
 
   // phase 2: one lane per MP
   if (!mine) return;
+  // The 1 to kTail pairs past the slots of a long row (where phase 1 left them).
+  // Their sum is formed as phase 1's lanes would form it, one pair per lane:
+  // ((c0 + c7) + (c2 + c5)) + ((c1 + c6) + (c3 + c4)), the products rounded
+  // before they are added.
+  const int64_t t0 = (PAIRED ? (row[tid] & ~(int64_t)1) : row[tid]) + kSlots * kGather;
+  const int n_tail = (int)(row[tid + 1] - t0);
+  if (!SMALL && n_tail > 0 && n_tail <= kTail && have_nodes &&
+      tails[tid % (kMpBlock / kGather) / (kWave / kGather)]) {
+    const double2* __restrict__ nd2 = reinterpret_cast<const double2*>(nodes);
+    // sums c0 .. c0 + NS - 1 of the NS per pass (a bound on the registers)
+    auto add_sums = [&](auto first) {
+#pragma clang fp contract(off)
+      constexpr int c0 = decltype(first)::value;
+      constexpr int NS = c0 + 6 <= kGathered ? 6 : kGathered - c0;
+      auto pair = [&](int j, double (&a)[NS]) {
+#pragma clang fp contract(off)
+        const int64_t q = t0 + (j < n_tail ? j : 0);
+        const int32_t J = idx[q];
+        const double w = N[q];
+        const double h[3] = {(double)dN[q], (double)dN[cap + q], (double)dN[2 * cap + q]};
+        const double2 ra = nd2[4 * (int64_t)J], rb = nd2[4 * (int64_t)J + 1];
+        const double2 rc = nd2[4 * (int64_t)J + 2];
+        const double x[3] = {ra.x, ra.y, rb.x}, u[3] = {rb.y, rc.x, rc.y};
+        double2 rd = make_double2(0.0, 0.0);
+        if constexpr (COND) rd = nd2[4 * (int64_t)J + 3];
+#pragma unroll
+        for (int e = 0; e < NS; ++e) {
+          const int c = c0 + e;
+          const double v = c < 3 ? w * x[c < 3 ? c : 0]
+                           : c < 12 ? u[(c - 3) / 3 % 3] * h[c % 3]
+                           : c < 15 ? rd.x * h[c % 3]
+                                    : w * rd.y;
+          a[e] = (j < n_tail ? v : 0.0) + 0.0;
+        }
+      };
+      double x[NS], y[NS], z[NS];
+      auto two = [&](int j, int k, double (&a)[NS]) {
+#pragma clang fp contract(off)
+        pair(j, a);
+        if (k < n_tail) {
+          double b[NS];
+          pair(k, b);
+#pragma unroll
+          for (int e = 0; e < NS; ++e) a[e] = a[e] + b[e];
+        }
+      };
+      auto plus = [&](double (&a)[NS], const double (&b)[NS]) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int e = 0; e < NS; ++e) a[e] = a[e] + b[e];
+      };
+      two(0, 7, x);
+      if (n_tail > 2) {
+        two(2, 5, y);
+        plus(x, y);
+      }
+      if (n_tail > 1) {
+        two(1, 6, y);
+        if (n_tail > 3) {
+          two(3, 4, z);
+          plus(y, z);
+        }
+        plus(x, y);
+      }
+#pragma unroll
+      for (int e = 0; e < NS; ++e) {
+        const int c = c0 + e;
+        double& s = sums[COND && c >= 12 ? c + 1 : c][tid];
+        s = s + x[e];
+      }
+    };
+    add_sums(std::integral_constant<int, 0>{});
+    add_sums(std::integral_constant<int, 6>{});
+    if constexpr (COND) add_sums(std::integral_constant<int, 12>{});
+  }
   M3<double> H;
 #pragma unroll
   for (int i = 0; i < 3; ++i)
