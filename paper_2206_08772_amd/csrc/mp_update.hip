@@ -216,7 +216,7 @@ void launch_node_update(const otm_state& st, const otm_params& p, double dt, boo
       p.wall_x[2], p.wall_n[0], p.wall_n[1], p.wall_n[2], zero_mf ? 1 : 0, packed, st.n_mp,
       diag, t, p.kappa > 0.0 ? st.heat : nullptr, p.Cp,
       boxes != nullptr ? reinterpret_cast<Box*>(boxes->bbox_part) : nullptr,
-      boxes != nullptr ? bin_counters(*boxes) : BinCounters{});
+      boxes != nullptr ? bin_counters(*boxes, st.n_mp) : BinCounters{});
 }
 
 // ----------------------------------------------------- material-point pass

@@ -13,9 +13,10 @@
 // hundred words they read and reduce themselves: the grid from the box
 // partials (in the count), the totals before a scan workgroup, the pairs
 // before a compaction group.  6 launches up to 8192 MPs and 16384 cells, 7 to 8
-// above, where up to 13 were needed; a step of up to 65536 nodes spares the box
-// launch too (the node update forms the partials).  Search of 4096 MPs: 32 us of kernel time,
-// 73 before; 27.6k: 47 (86); 108k: 77 (99); 1.13M: 301 (352).
+// above, where up to 13 were needed, and two fewer where the fill scans the cells
+// (few_cells) and, in a step of up to 65536 nodes, the node update forms the box
+// partials.  Search of 4374 MPs in a step: 25 us of kernel time, 73 before;
+// 27.8k: 40 (86); 108k: 73 (99); 1.13M: 301 (352).
 #include <type_traits>
 
 #include "boxes.h"
@@ -270,7 +271,8 @@ struct BinSet {
   int64_t n;
   int32_t* cell;       // [n] cell of each point
   int32_t* rank;       // [n] its place among the cell's points
-  int32_t* start;      // [cap + 1] counts, then offsets
+  int32_t* cnt;        // [cap + 1] counts, from [1] on
+  int32_t* start;      // [cap + 1] offsets (the same place, with many cells)
   double4* sorted;     // [n] (x, y, z, index) in cell order
 };
 constexpr unsigned kCountBlocks = 2048;  // of the count: as many as fit at once
@@ -284,6 +286,7 @@ OTM_DEV bool bin_pick(const BinSet& a, const BinSet& b, int64_t b0, int64_t t, B
   set.n = first ? a.n : b.n;
   set.cell = first ? a.cell : b.cell;
   set.rank = first ? a.rank : b.rank;
+  set.cnt = first ? a.cnt : b.cnt;
   set.start = first ? a.start : b.start;
   set.sorted = first ? a.sorted : b.sorted;
   return i >= 0 && i < set.n;
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(256) void k_bin_count(BinSet a, BinSet b, int64_t b
       const int cz = cell_coord(x[2], g.lo[2], inv, g.dims[2]);
       const int32_t cid = (cz * g.dims[1] + cy) * g.dims[0] + cx;
       set.cell[i] = cid;
-      set.rank[i] = grouped_atomic_add(set.start + 1, cid);
+      set.rank[i] = grouped_atomic_add(set.cnt + 1, cid);
     }
     t += (int64_t)gridDim.x * 256;
     any = t < n_threads && bin_pick(a, b, b0, t, set, i);
@@ -342,6 +345,48 @@ __global__ __launch_bounds__(256) void k_bin_fill(BinSet a, BinSet b, int64_t b0
   const int64_t n = set.n;
   const int32_t pos = set.start[set.cell[i]] + set.rank[i];
   set.sorted[pos] = make_double4(x[i], x[n + i], x[2 * n + i], (double)i);
+}
+
+// The fill of few cells (few_cells): the offsets of the sets that the workgroup
+// needs are scanned in LDS; the first workgroup keeps them for the passes that
+// follow.
+__global__ __launch_bounds__(256) void k_bin_scan_fill(BinSet a, BinSet b, int64_t b0,
+                                                       const Grid* __restrict__ gp) {
+  __shared__ int32_t off[2][kFewCells];
+  __shared__ int32_t sums[2][256 / kWave];
+  const int tid = threadIdx.x;
+  const int64_t t = (int64_t)blockIdx.x * 256;
+  BinSet set;
+  int64_t i;
+  const bool any = bin_pick(a, b, b0, t + tid, set, i);
+  double x[3] = {0.0, 0.0, 0.0};
+  int32_t cell = 0, rank = 0;
+  if (any) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = set.x[c * set.n + i];
+    cell = set.cell[i];
+    rank = set.rank[i];
+  }
+  const int n_cells = (int)gp->n_cells;
+  const int per = (n_cells + 255) / 256;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const BinSet& q = s == 0 ? a : b;
+    if (blockIdx.x != 0 && !(s == 0 ? t < a.n : t + 256 > b0)) continue;  // uniform
+    int32_t sum = 0, total;
+    for (int e = tid * per; e < (tid + 1) * per && e < n_cells; ++e) {
+      off[s][e] = sum;
+      sum += q.cnt[1 + e];
+    }
+    const int32_t before = block_scan(sum, sums[s], total);
+    for (int e = tid * per; e < (tid + 1) * per && e < n_cells; ++e) off[s][e] += before;
+    __syncthreads();
+    if (blockIdx.x == 0)
+      for (int e = tid; e <= n_cells; e += 256) q.start[e] = e < n_cells ? off[s][e] : total;
+  }
+  if (any)
+    set.sorted[off[t + tid < a.n ? 0 : 1][cell] + rank] =
+        make_double4(x[0], x[1], x[2], (double)i);
 }
 
 // ---------------------------------------------------------------- MP lists
@@ -928,24 +973,30 @@ void launch_search(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const d
     k_search_empty<<<1, 1, 0, s>>>(nbr_offsets, diag);
     return;
   }
+  const BinCounters z = bin_counters(w, n_mp);
   Box* part = reinterpret_cast<Box*>(w.bbox_part);
   unsigned n_part = (unsigned)((n_nodes + 255) / 256);
   if (!boxed) {
     n_part = bbox_blocks(n_nodes);
-    k_bbox_partial<<<n_part, 256, 0, s>>>(x_nodes, n_nodes, part, bin_counters(w));
+    k_bbox_partial<<<n_part, 256, 0, s>>>(x_nodes, n_nodes, part, z);
   }
   // nodes and MPs binned on the grid together: one count, one two-array scan,
   // one fill.  The MPs' ranks lie where their rows are staged later.
-  const BinSet nodes{x_nodes, n_nodes, w.node_cell, w.node_rank, w.cell_start, w.sorted};
-  const BinSet mps{x_mp, n_mp, w.mp_cell, w.stage, w.mp_cell_start, w.mp_sorted};
+  const BinSet nodes{x_nodes, n_nodes, w.node_cell, w.node_rank, z.node_cnt, w.cell_start,
+                     w.sorted};
+  const BinSet mps{x_mp, n_mp, w.mp_cell, w.stage, z.mp_cnt, w.mp_cell_start, w.mp_sorted};
   const int64_t b0 = (n_nodes + kWave - 1) / kWave * kWave;
   const int64_t nt = b0 + n_mp;
   const unsigned nbt = (unsigned)((nt + 255) / 256);
   k_bin_count<<<nbt < kCountBlocks ? nbt : kCountBlocks, 256, 0, s>>>(
       nodes, mps, b0, part, (int)n_part, cell_size, w.cap_cells, w.grid);
-  scan_impl<int32_t>(w.cell_start + 1, w.mp_cell_start + 1, w.cap_cells, w.scan_aux,
-                     &w.grid->n_cells, s);
-  k_bin_fill<<<nbt, 256, 0, s>>>(nodes, mps, b0);
+  if (few_cells(w, n_mp)) {
+    k_bin_scan_fill<<<nbt, 256, 0, s>>>(nodes, mps, b0, w.grid);
+  } else {
+    scan_impl<int32_t>(w.cell_start + 1, w.mp_cell_start + 1, w.cap_cells, w.scan_aux,
+                       &w.grid->n_cells, s);
+    k_bin_fill<<<nbt, 256, 0, s>>>(nodes, mps, b0);
+  }
   const double r2 = r_list * r_list;
   // a fixed grid (a multiple of the 8 XCDs) strides over the items.  The MPs'
   // cells are not needed any more: their counts take that place.

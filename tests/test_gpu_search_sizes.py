@@ -1,7 +1,7 @@
 """Support lists against a brute-force float64 search, bit for bit: MP counts at
 the edges of a compaction group (64), of a run of counts (16384) and of the direct
-path (8192); few cells, whose MPs are split among waves, and more than one scan
-workgroup of cells; rows around 32, 40 and 64 ids; capacities that do not fit."""
+path (8192); few cells, whose MPs are split among waves and which the fill scans
+itself, and more than one scan workgroup of cells; rows around 32, 40 and 64 ids; capacities that do not fit."""
 import numpy as np
 import pytest
 import torch
@@ -46,12 +46,22 @@ def test_one_cell_rows_of_one_length(n_nodes):
     assert (rows == n_nodes).all()
 
 
-def test_cells_of_two_scan_workgroups():
+@pytest.mark.parametrize("side,n_mp", [(19, 200), (19, 9000), (20, 9000), (27, 9000)])
+def test_many_cells(side, n_mp):
+    """Cells scanned by the fill, up to near its limit of 8192, by one scan
+    workgroup, and by two (27^3 cells of edge 0.98)."""
     rng = np.random.default_rng(5)
-    g = np.arange(27.0)
+    g = np.arange(float(side))
     X = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
-    X = X + rng.uniform(-0.02, 0.02, X.shape)            # 27^3 cells of edge 0.98
-    check(X, rng.uniform(-1, 27, (9000, 3)), 0.97, 0.98)
+    X = X + rng.uniform(-0.02, 0.02, X.shape)
+    check(X, rng.uniform(-1, side, (n_mp, 3)), 0.97, 0.98)
+
+
+@pytest.mark.parametrize("n_mp", [65536, 65537])
+def test_many_mps_in_few_cells(n_mp):
+    rng = np.random.default_rng(n_mp)
+    X = rng.uniform(0, 1, (500, 3))
+    check(X, rng.uniform(0, 1, (n_mp, 3)), 0.2, 0.21)
 
 
 @pytest.mark.parametrize("n_mp", [500, 8192, 9000])
