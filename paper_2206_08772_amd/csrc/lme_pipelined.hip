@@ -89,9 +89,16 @@ OTM_DEV double lme_exp_small(double t) {
 // Sum over the four lanes of an MP's group (lanes c, c + 16, c + 32, c + 48 of
 // the wave), in each of them: the product of a 4x4 block of ones with the four
 // lanes' values on the matrix cores, which leaves the vector ALU to the other
-// waves (one instruction for six).
+// waves (one instruction for six).  Only where the whole wave is active: the
+// matrix cores write every lane's result, also those of lanes that a branch or
+// a loop has switched off, whose values the same registers may still hold.
 OTM_DEV double rows_sum(double v) {
   return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
+}
+// The same where groups have parted (each group's lanes stay together).
+OTM_DEV double rows_sum_parted(double v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
 }
 OTM_DEV double rows_max(double v) {
   v = fmax(v, __shfl_xor(v, 16));
@@ -108,11 +115,17 @@ struct Sums {
     s0 += e * dx * dx; s1 += e * dy * dy; s2 += e * dz * dz;
     s3 += e * dx * dy; s4 += e * dy * dz; s5 += e * dx * dz;
   }
-  OTM_DEV void reduce() {
+  OTM_DEV void reduce() {  // the whole wave's groups together
     Z = rows_sum(Z);
     r0 = rows_sum(r0); r1 = rows_sum(r1); r2 = rows_sum(r2);
     s0 = rows_sum(s0); s1 = rows_sum(s1); s2 = rows_sum(s2);
     s3 = rows_sum(s3); s4 = rows_sum(s4); s5 = rows_sum(s5);
+  }
+  OTM_DEV void reduce_parted() {
+    Z = rows_sum_parted(Z);
+    r0 = rows_sum_parted(r0); r1 = rows_sum_parted(r1); r2 = rows_sum_parted(r2);
+    s0 = rows_sum_parted(s0); s1 = rows_sum_parted(s1); s2 = rows_sum_parted(s2);
+    s3 = rows_sum_parted(s3); s4 = rows_sum_parted(s4); s5 = rows_sum_parted(s5);
   }
 };
 
@@ -498,7 +511,7 @@ OTM_DEV Solve lme_solve(const double (&d)[kPpl][3], double (&e)[kPpl], const Slo
 }
 
 // One MP's solve with its pairs re-read from memory at every evaluation, and
-// its stores.
+// its stores.  The wave's MPs go their own ways in it.
 template <bool PACKED, class Sink>
 OTM_DEV void lme_uncached(const LmeArgs<PACKED>& a, const typename Sink::In& in, int64_t p,
                           int lane, int64_t off, int K, Sink& sink) {
@@ -522,7 +535,7 @@ OTM_DEV void lme_uncached(const LmeArgs<PACKED>& a, const typename Sink::In& in,
       const double f = pair(q);
       s.add(lme_exp(f - shift), dx, dy, dz);
     }
-    s.reduce();
+    s.reduce_parted();
   };
   const double tol2 = a.tol * a.tol;
   Eval ev;

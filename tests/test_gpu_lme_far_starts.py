@@ -1,0 +1,149 @@
+"""The pipelined shape-function kernel (131,072 MPs and more, float64) from start
+multipliers far from the solution and on bodies whose Newton steps are cut back,
+where an MP's neighbours in the wave take other numbers of trials: N and grad N
+must be those of the returned multiplier, formed in plain float64, and every MP
+that the kernel of smaller calls solves must be solved."""
+import numpy as np
+import pytest
+import torch
+
+import otm_workloads as W
+from tests.gpu_common import make_sim, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+N_MP = 4 * 512 * 64
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    require_gpu()
+
+
+def cloud(stretch, lam_size, far, seed=3):
+    """Jittered lattice of spacing 1 stretched along x, MPs inside it in Z-order,
+    and start multipliers: 0, or normal ones for the share ``far`` of the MPs."""
+    rng = np.random.default_rng(seed)
+    g = np.arange(24.0)
+    x = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    x = x + rng.uniform(-0.1, 0.1, x.shape)
+    xp = rng.uniform(2.0, 21.0, (N_MP, 3))
+    i = (xp * 4).astype(np.int64)
+    xp = xp[np.argsort(W._morton3(i[:, 0], i[:, 1], i[:, 2]))]
+    lam = lam_size * rng.standard_normal((N_MP, 3))
+    lam[rng.uniform(size=N_MP) >= far] = 0.0
+    s = np.array([stretch, 1.0, 1.0])
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a.T)).cuda()  # noqa: E731
+    return dev(x * s), dev(xp * s), dev(lam)
+
+
+def sums(mp, n, v):
+    out = torch.zeros(v.shape[:-1] + (n,), dtype=torch.float64, device="cuda")
+    return out.index_add_(out.dim() - 1, mp, v)
+
+
+def plain(d, mp, n, beta, lam):
+    """Weights, residual and J of the multipliers, in plain float64."""
+    f = -beta * (d * d).sum(0) + (lam[:, mp] * d).sum(0)
+    top = torch.full((n,), -torch.inf, dtype=torch.float64, device="cuda")
+    top = top.scatter_reduce(0, mp, f, "amax")
+    w = torch.exp(f - top[mp])
+    w = w / sums(mp, n, w)[mp]
+    r = sums(mp, n, w * d)
+    J = torch.stack([sums(mp, n, w * d[i] * d[j]) - r[i] * r[j]
+                     for i in range(3) for j in range(3)], -1).reshape(n, 3, 3)
+    return f.abs().nan_to_num(torch.inf), w, r.norm(dim=0), J
+
+
+def check_own_multiplier(d, mp, n, beta, lam, N, dN, rows, unit=1.0):
+    """N and grad N (of lengths measured in ``unit``) against the plain ones at
+    ``lam``, in the given rows; returns the plain residual and a lower bound of
+    J's smallest eigenvalue."""
+    f, w, r, J = plain(d, mp, n, beta, lam)
+    det = torch.linalg.det(J.cpu()).cuda()
+    tr = J.diagonal(dim1=1, dim2=2).sum(1)
+    lo = 4.0 * det / tr ** 2                      # det / (product of the two larger ones)
+    # an exponent's rounding is a few ulps of the largest exponent, here below 1e3
+    # (2e-13 each): 40 of them in a weight's relative error
+    use = rows[mp] & (f < 1e3)
+    assert float(use.double().mean()) > 0.9
+    assert float((N - w)[use].abs().max()) < 1e-11
+    assert float((sums(mp, n, N) - 1.0)[rows].abs().max()) < 1e-12
+    # grad N = -N J^-1 d: the weights' error passes to J and is divided by its
+    # eigenvalues twice
+    well = use & (lo > 0.02)[mp]
+    assert float(well.double().mean()) > 0.3
+    Ji = torch.linalg.inv(torch.where((lo > 0.02)[:, None, None], J,
+                                      torch.eye(3, dtype=torch.float64, device="cuda")).cpu()).cuda()
+    g = -w * torch.stack([sum(Ji[mp, i, j] * d[j] for j in range(3)) for i in range(3)])
+    assert float(((dN * unit - g).abs() * lo[mp] ** 2)[:, well].max()) < 1e-10
+    return r, lo
+
+
+def solved_by_small_calls(x, xp, offsets, idx, beta, lam):
+    """The rows that the kernel of smaller calls solves."""
+    from paper_2206_08772_amd.sim import lme_shape
+    rows = torch.diff(offsets)
+    h = N_MP // 2
+    out = []
+    for a, b in ((0, h), (h, N_MP)):
+        q0, q1 = int(offsets[a]), int(offsets[b])
+        part = idx[q0:q1].contiguous()
+        o = (offsets[a:b + 1] - q0).contiguous()
+        l2, _, _, _ = lme_shape(x, xp[:, a:b].contiguous(), o, part, beta, 1e-13,
+                                lam=lam[:, a:b].contiguous())
+        mp = torch.arange(b - a, device="cuda").repeat_interleave(rows[a:b])
+        d = xp[:, a:b][:, mp] - x[:, part.long()]
+        out.append(plain(d, mp, b - a, beta, l2)[2] <= 1e-12)
+    return torch.cat(out)
+
+
+def run(stretch, gamma, radius, lam_size, far, long_rows):
+    from paper_2206_08772_amd.sim import build_neighbors, lme_shape, read_diag
+    x, xp, lam0 = cloud(stretch, lam_size, far)
+    offsets, idx = build_neighbors(x, xp, radius, radius * 1.0001)
+    rows = torch.diff(offsets)
+    want = solved_by_small_calls(x, xp, offsets, idx, gamma, lam0)
+    lam, N, dN, diag = lme_shape(x, xp, offsets, idx, gamma, 1e-13, lam=lam0.clone())
+    _, dg = read_diag(diag)
+    take = rows > 40 if long_rows else (rows > 0) & (rows <= 40)
+    assert float(take.double().mean()) > 0.9
+    want = want & take
+    assert float(want.double().mean()) > 0.9
+    mp = torch.arange(N_MP, device="cuda").repeat_interleave(rows)
+    d = xp[:, mp] - x[:, idx.long()]
+    r, _ = check_own_multiplier(d, mp, N_MP, gamma, lam, N, dN, want)
+    assert float(r[want].max()) <= 1e-12
+    assert dg.n_lme_noconv <= N_MP - int(want.sum())
+
+
+# rows past 40 pairs, solved from memory: an MP at its start in one group of lanes
+# while the next one's trials go on
+@pytest.mark.parametrize("lam_size,far", [(8.0, 0.3), (4.0, 1.0)])
+def test_long_rows_keep_their_sums(lam_size, far):
+    run(1.0, 4.0, 2.4, lam_size, far, long_rows=True)
+
+
+def test_long_rows_keep_their_sums_in_a_body():
+    """The same with the fused assembly: nodal masses of the far starts' N."""
+    w = W.taylor_rod(h=3.2e-3 / 10.6, seed=2, length=22.4e-3, skin_h=0.4)
+    assert w.n_mp >= N_MP
+    sim, p = make_sim(w)
+    sim.init()
+    rng = np.random.default_rng(5)
+    lam = 8.0 / w.h * rng.standard_normal((3, w.n_mp))
+    lam[:, rng.uniform(size=w.n_mp) >= 0.3] = 0.0
+    sim.lam.copy_(torch.from_numpy(lam))
+    sim.refresh(rebuild=False)
+    off = sim.offsets
+    P = int(off[-1])
+    rows = torch.diff(off)
+    assert float((rows > 40).double().mean()) > 0.3
+    mp = torch.arange(w.n_mp, device="cuda").repeat_interleave(rows)
+    I = sim.idx[:P].long()
+    N = sim.N[:P]
+    total = sums(mp, w.n_mp, N)
+    assert float((total - 1.0)[rows > 40].abs().max()) < 1e-12
+    got, pair = sim.m, N * sim.mass[mp]
+    want = torch.zeros_like(got).index_add_(0, I, pair)
+    assert float(((got - want).abs() - 1e-13 * want).max()) <= 0.0
