@@ -33,7 +33,8 @@
 //    of evaluating them anew, and needs no line search: with the cumulants
 //    kappa_k of delta . d, kappa_1 = -kappa_2 for a Newton step, the change of
 //    log Z, sum_k kappa_k / k!, is below -0.47 kappa_2, far past the Armijo bound
-//    1e-4 slope = -1e-4 kappa_2.  Larger steps multiply by the full exp.
+//    1e-4 slope = -1e-4 kappa_2.  At most kSmallSteps such steps follow one
+//    another (roundings add up); every other evaluation forms the weights anew.
 //  - The sums over a group run on the matrix cores.
 #include <type_traits>
 
@@ -79,6 +80,7 @@ struct NodeSrc {
 
 // exp(t) for |t| <= kSmallStep.
 constexpr double kSmallStep = 1.0 / 32.0;
+constexpr int kSmallSteps = 8;  // in a row
 OTM_DEV double lme_exp_small(double t) {
   double p = kExpTaylorPipelined[7];
 #pragma unroll
@@ -415,11 +417,10 @@ struct LmeArgs {
 };
 
 // Newton iteration of the wave's rows in registers (every lane takes part; rows
-// without pairs, and done ones, go along with steps of 0, which change
-// nothing).  The multiplier is advanced in place, e ends as the weights (0
-// past the row) and Mi as J^{-1} at it.  Solve::Leave: not a row (live false),
-// or the weights left the range in which their sum is accurate; the row is
-// to be solved from memory.
+// without pairs, and done ones, go along with steps of 0).  The multiplier is
+// advanced in place, e ends as the weights (0 past the row) and Mi as J^{-1}
+// at it.  Solve::Leave: not a row (live false), or sums that are not numbers;
+// the row is to be solved from memory.
 enum class Solve { Converged, Failed, Leave };
 
 OTM_DEV Solve lme_solve(const double (&d)[kPpl][3], double (&e)[kPpl], const Slots& sl, bool live,
@@ -433,71 +434,37 @@ OTM_DEV Solve lme_solve(const double (&d)[kPpl][3], double (&e)[kPpl], const Slo
     r2 = fmax(r2, fma(d[k][0], d[k][0], fma(d[k][1], d[k][1], d[k][2] * d[k][2])));
   const float br2 = fmaxf((float)(beta * rows_sum(r2)) * 1.00001f, 1e-30f);
   Sums s;
-  s.clear();
-  // the weights at lam, their exponents shifted by |lam|^2 / (4 beta), the
-  // largest one any offset can have
-  {
-    const double shift = (lam[0] * lam[0] + lam[1] * lam[1] + lam[2] * lam[2]) / (4.0 * beta);
+  double shift;
+  // the weights at lam, formed from the prior, their exponents shifted by the
+  // row's largest (an unused slot's is its first pair's)
+  auto anew = [&]() {
+    double top = -INFINITY, b = beta;
+    __asm__ volatile("" : "+s"(b));  // (kept from holding the priors in registers)
     sl.each([&](int k) {
-      const double prior = -beta * ((d[k][0] * d[k][0] + d[k][1] * d[k][1]) +
-                                    d[k][2] * d[k][2]);
-      const double w =
-          lme_exp(prior + (lam[0] * d[k][0] + lam[1] * d[k][1] + lam[2] * d[k][2]) - shift);
-      e[k] = sl.has(k) ? w : 0.0;
-      s.add(e[k], d[k][0], d[k][1], d[k][2]);
+      e[k] = (lam[0] - b * d[k][0]) * d[k][0] + (lam[1] - b * d[k][1]) * d[k][1] +
+             (lam[2] - b * d[k][2]) * d[k][2];
+      top = fmax(top, e[k]);
     });
-    s.reduce();
-  }
-  // the weights moved by the change a of the multiplier
-  auto move = [&](const double (&a)[3], auto small) {
+    shift = rows_max(top);
     s.clear();
     sl.each([&](int k) {
-      const double t = a[0] * d[k][0] + a[1] * d[k][1] + a[2] * d[k][2];
-      e[k] *= decltype(small)::value ? lme_exp_small(t) : lme_exp(t);
+      const double w = lme_exp(e[k] - shift);
+      e[k] = sl.has(k) ? w : 0.0;
       s.add(e[k], d[k][0], d[k][1], d[k][2]);
     });
     s.reduce();
   };
   Solve res = Solve::Leave;
   const double tol2 = tol * tol;
-  for (int it = 0;; ++it) {
-    Eval ev;
-    ev.from(s);
-    iz = ev.iz;
-    double det, a[3];
-    sym_inv(ev.J, Mi, det);
-    const bool step = newton_step(ev, Mi, det, a);
-    if (live) {
-      if (ev.r[0] * ev.r[0] + ev.r[1] * ev.r[1] + ev.r[2] * ev.r[2] <= tol2)
-        res = Solve::Converged;
-      else if (s.Z > 1e-200 && s.Z < 1e200 && (it >= max_iter || !step))
-        res = Solve::Failed;
-      else
-        live = s.Z > 1e-200 && s.Z < 1e200;
-      live = live && res == Solve::Leave;
-    }
-    if (__ballot(live) == 0) return res;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      a[c] = live ? a[c] : 0.0;
-      lam[c] += a[c];
-    }
-    const double a2 = a[0] * a[0] + a[1] * a[1] + a[2] * a[2];
-    const bool small = a2 * (double)br2 <= kSmallStep * kSmallStep * beta;
-    if (__ballot(!small) == 0) {
-      move(a, std::true_type{});
-      continue;
-    }
-    // trials at 1, 1/2, 1/4, ... of the steps that are not small, each reached
-    // from the last one (the weights keep their shift, so their sums compare
-    // as they are)
-    double drop = 1e-4 * (ev.r[0] * a[0] + ev.r[1] * a[1] + ev.r[2] * a[2]);
-    double from = log(s.Z);
-    from += 1e-12 * (1.0 + fabs(from));
-    bool open = !small;
+  double a[3] = {0.0, 0.0, 0.0}, from = 0.0, drop = 0.0;
+  bool open = false;
+  for (int it = 0;;) {
+    // trials at 1, 1/2, 1/4, ... of the steps that are not small (at first, the
+    // start), the weights formed anew at each: a rejected trial can be so far
+    // off that weights which matter vanish at it, and no factor brings them back
     for (int h = 0;; ++h) {
-      move(a, std::false_type{});
-      open = open && !(log(s.Z) <= from + drop);
+      anew();
+      open = open && !(log(s.Z) + shift <= from + drop);
       if (h == 30 || __ballot(open) == 0) break;
       const double back = !open ? 0.0 : (h == 0 ? -0.5 : 0.5);
 #pragma unroll
@@ -506,6 +473,46 @@ OTM_DEV Solve lme_solve(const double (&d)[kPpl][3], double (&e)[kPpl], const Slo
         lam[c] += a[c];
       }
       drop *= 0.5;
+    }
+    // Newton steps from the weights at lam, up to one that is not small
+    for (int since = 0;; ++since, ++it) {
+      Eval ev;
+      ev.from(s);
+      iz = ev.iz;
+      double det;
+      sym_inv(ev.J, Mi, det);
+      const bool step = newton_step(ev, Mi, det, a);
+      if (live) {
+        if (ev.r[0] * ev.r[0] + ev.r[1] * ev.r[1] + ev.r[2] * ev.r[2] <= tol2)
+          res = Solve::Converged;
+        else if (s.Z < INFINITY && (it >= max_iter || !step))
+          res = Solve::Failed;
+        else
+          live = s.Z < INFINITY;
+        live = live && res == Solve::Leave;
+      }
+      if (__ballot(live) == 0) return res;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        a[c] = live ? a[c] : 0.0;
+        lam[c] += a[c];
+      }
+      const double a2 = a[0] * a[0] + a[1] * a[1] + a[2] * a[2];
+      open = live && !(a2 * (double)br2 <= kSmallStep * kSmallStep * beta);
+      if (__ballot(open) != 0 || since == kSmallSteps) {
+        from = log(s.Z) + shift;
+        from += 1e-12 * (1.0 + fabs(from));
+        drop = 1e-4 * (ev.r[0] * a[0] + ev.r[1] * a[1] + ev.r[2] * a[2]);
+        ++it;
+        break;
+      }
+      // the weights moved with the multiplier
+      s.clear();
+      sl.each([&](int k) {
+        e[k] *= lme_exp_small(a[0] * d[k][0] + a[1] * d[k][1] + a[2] * d[k][2]);
+        s.add(e[k], d[k][0], d[k][1], d[k][2]);
+      });
+      s.reduce();
     }
   }
 }
@@ -747,10 +754,17 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
     set_row(o[0], o[1], mine < n1, even1, front1, rel1, K1);
   }
   for (;;) {
-    // (places recomputed in each pass rather than held in registers)
-    int tv = (int)(wave * kWave + __lane_id());
-    __asm__ volatile("" : "+v"(tv));
-    const int wl = tv % kWave, lane = wl / kWaveMps, mine = tv / kWave * kWaveMps + wl % kWaveMps;
+    // (places recomputed in each pass, and after the solve, rather than held in
+    // registers)
+    int tv, wl, lane, mine;
+    auto places = [&]() {
+      tv = (int)(wave * kWave + __lane_id());
+      __asm__ volatile("" : "+v"(tv));
+      wl = tv % kWave;
+      lane = wl / kWaveMps;
+      mine = tv / kWave * kWaveMps + wl % kWaveMps;
+    };
+    places();
     const Place w2 = after(w1);
     const int n2 = count(w2);
     const bool fits1 = K1 > 0 && K1 <= kRowMax;
@@ -777,6 +791,7 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
     }
     const Slots sl(lim);
     const Solve res = lme_solve(d, e, sl, fits, c0.a.beta, c0.a.tol, c0.a.max_iter, lam, iz, Mi);
+    places();
     const Call& c1 = kernel_arg<Call>();
     const bool add = res != Solve::Leave;
     if (lane == 0 && add) {

@@ -21,8 +21,9 @@ def _gpu():
 
 
 def cloud(stretch, lam_size, far, seed=3):
-    """Jittered lattice of spacing 1 stretched along x, MPs inside it in Z-order,
-    and start multipliers: 0, or normal ones for the share ``far`` of the MPs."""
+    """Jittered lattice of spacing 1 stretched along x (by the two factors on
+    either side of its middle), MPs inside it in Z-order, and start multipliers:
+    0, or normal ones for the share ``far`` of the MPs."""
     rng = np.random.default_rng(seed)
     g = np.arange(24.0)
     x = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
@@ -32,9 +33,10 @@ def cloud(stretch, lam_size, far, seed=3):
     xp = xp[np.argsort(W._morton3(i[:, 0], i[:, 1], i[:, 2]))]
     lam = lam_size * rng.standard_normal((N_MP, 3))
     lam[rng.uniform(size=N_MP) >= far] = 0.0
-    s = np.array([stretch, 1.0, 1.0])
+    for a in (x, xp):
+        a[:, 0] = np.where(a[:, 0] < 11.5, stretch[0], stretch[1]) * (a[:, 0] - 11.5)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a.T)).cuda()  # noqa: E731
-    return dev(x * s), dev(xp * s), dev(lam)
+    return dev(x), dev(xp), dev(lam)
 
 
 def sums(mp, n, v):
@@ -66,13 +68,13 @@ def check_own_multiplier(d, mp, n, beta, lam, N, dN, rows, unit=1.0):
     # an exponent's rounding is a few ulps of the largest exponent, here below 1e3
     # (2e-13 each): 40 of them in a weight's relative error
     use = rows[mp] & (f < 1e3)
-    assert float(use.double().mean()) > 0.9
+    assert int(use.sum()) > 0.9 * int(rows[mp].sum())
     assert float((N - w)[use].abs().max()) < 1e-11
     assert float((sums(mp, n, N) - 1.0)[rows].abs().max()) < 1e-12
     # grad N = -N J^-1 d: the weights' error passes to J and is divided by its
     # eigenvalues twice
     well = use & (lo > 0.02)[mp]
-    assert float(well.double().mean()) > 0.3
+    assert int(well.sum()) > 0.3 * int(use.sum())
     Ji = torch.linalg.inv(torch.where((lo > 0.02)[:, None, None], J,
                                       torch.eye(3, dtype=torch.float64, device="cuda")).cpu()).cuda()
     g = -w * torch.stack([sum(Ji[mp, i, j] * d[j] for j in range(3)) for i in range(3)])
@@ -106,10 +108,11 @@ def run(stretch, gamma, radius, lam_size, far, long_rows):
     want = solved_by_small_calls(x, xp, offsets, idx, gamma, lam0)
     lam, N, dN, diag = lme_shape(x, xp, offsets, idx, gamma, 1e-13, lam=lam0.clone())
     _, dg = read_diag(diag)
+    assert 31 <= float(rows.double().mean()) <= 38     # rows for the pipelined kernel
     take = rows > 40 if long_rows else (rows > 0) & (rows <= 40)
-    assert float(take.double().mean()) > 0.9
+    assert float(take.double().mean()) > 0.3
     want = want & take
-    assert float(want.double().mean()) > 0.9
+    assert float(want.double().mean()) > 0.9 * float(take.double().mean())
     mp = torch.arange(N_MP, device="cuda").repeat_interleave(rows)
     d = xp[:, mp] - x[:, idx.long()]
     r, _ = check_own_multiplier(d, mp, N_MP, gamma, lam, N, dN, want)
@@ -121,12 +124,12 @@ def run(stretch, gamma, radius, lam_size, far, long_rows):
 # while the next one's trials go on
 @pytest.mark.parametrize("lam_size,far", [(8.0, 0.3), (4.0, 1.0)])
 def test_long_rows_keep_their_sums(lam_size, far):
-    run(1.0, 4.0, 2.4, lam_size, far, long_rows=True)
+    run((1.3, 0.75), 4.0, 2.0, lam_size, far, long_rows=True)
 
 
 def test_long_rows_keep_their_sums_in_a_body():
     """The same with the fused assembly: nodal masses of the far starts' N."""
-    w = W.taylor_rod(h=3.2e-3 / 10.6, seed=2, length=22.4e-3, skin_h=0.4)
+    w = W.taylor_rod(h=3.2e-3 / 10.6, seed=2, length=22.4e-3, skin_h=0.2)
     assert w.n_mp >= N_MP
     sim, p = make_sim(w)
     sim.init()
@@ -138,7 +141,7 @@ def test_long_rows_keep_their_sums_in_a_body():
     off = sim.offsets
     P = int(off[-1])
     rows = torch.diff(off)
-    assert float((rows > 40).double().mean()) > 0.3
+    assert float(rows.double().mean()) <= 38 and int((rows > 40).sum()) > 1000
     mp = torch.arange(w.n_mp, device="cuda").repeat_interleave(rows)
     I = sim.idx[:P].long()
     N = sim.N[:P]
@@ -147,3 +150,38 @@ def test_long_rows_keep_their_sums_in_a_body():
     got, pair = sim.m, N * sim.mass[mp]
     want = torch.zeros_like(got).index_add_(0, I, pair)
     assert float(((got - want).abs() - 1e-13 * want).max()) <= 0.0
+
+
+# rows in registers: bodies whose first steps are cut back (stretched, or with a
+# narrow prior), and far starts
+@pytest.mark.parametrize("stretch,gamma,radius,lam_size,far", [
+    (1.5, 4.0, 2.3, 0.0, 0.0), (1.6, 4.0, 2.35, 0.0, 0.0), (1.0, 9.0, 2.0, 0.0, 0.0),
+    (1.0, 10.0, 2.0, 0.0, 0.0), (1.0, 4.0, 2.0, 8.0, 0.3), (1.0, 4.0, 2.0, 8.0, 1.0)])
+def test_rejected_trials_leave_the_weights_exact(stretch, gamma, radius, lam_size, far):
+    run((stretch, stretch), gamma, radius, lam_size, far, long_rows=False)
+
+
+@pytest.mark.parametrize("scatter", ["atomic", "segmented"])
+def test_rejected_trials_in_a_body(scatter):
+    """The same in the step's variants of the kernel."""
+    w = W.taylor_rod(h=3.2e-3 / 10.6, seed=2, length=22.4e-3, skin_h=0.12)
+    assert w.n_mp >= N_MP
+    sim, p = make_sim(w, scatter=scatter)
+    sim.init()
+    rng = np.random.default_rng(6)
+    lam = 8.0 / w.h * rng.standard_normal((3, w.n_mp))
+    lam[:, rng.uniform(size=w.n_mp) >= 0.3] = 0.0
+    sim.lam.copy_(torch.from_numpy(lam))
+    assert sim.check_diag()[1].n_lme_noconv == 0
+    sim.refresh(rebuild=False)
+    _, dg = sim.check_diag(raise_on_error=False)
+    off = sim.offsets
+    P = int(off[-1])
+    rows = torch.diff(off)
+    assert 31 <= float(rows.double().mean()) <= 38
+    mp = torch.arange(w.n_mp, device="cuda").repeat_interleave(rows)
+    d = sim.xp[:, mp] - sim.x[:, sim.idx[:P].long()]
+    r, _ = check_own_multiplier(d / w.h, mp, w.n_mp, p["beta"] * w.h ** 2, sim.lam * w.h,
+                                sim.N[:P], sim.dN[:, :P], rows > 0, unit=w.h)
+    # the plain residual repeats the kernel's to a few roundings of its terms
+    assert int((r > p["lme_tol"] / w.h + 1e-13).sum()) <= dg.n_lme_noconv < 0.05 * w.n_mp
