@@ -29,11 +29,19 @@ OTM_DEV double lme_exp(const double* taylor, double x) {
   return x < -745.0 ? 0.0 : e;
 }
 
-// The pipelined kernel (lme_pipelined.hip), OTM_FP64.
+// Totals of pairs (none with lo > hi).
+struct PairWindow {
+  int64_t lo, hi;
+  OTM_DEV bool holds(int64_t pairs) const { return pairs >= lo && pairs <= hi; }
+};
+
+// The pipelined kernel (lme_pipelined.hip), OTM_FP64: it works on lists of `mine`
+// pairs in all and leaves others untouched.
 void launch_lme_pipelined(int64_t n_nodes, const double* x_nodes, int64_t n_mp,
                           const double* x_mp, const int64_t* nbr_offsets, const int32_t* nbr_idx,
                           int64_t pair_capacity, double beta, double tol, int32_t max_iter,
-                          double* lam, double* N, double* dN, const double4* packed, otm_diag* diag, hipStream_t s,
-                          const AsmIn* fused, const SegIn* seg);
+                          double* lam, double* N, double* dN, const double4* packed,
+                          otm_diag* diag, PairWindow mine, hipStream_t s, const AsmIn* fused,
+                          const SegIn* seg);
 
 }  // namespace otm

@@ -436,12 +436,14 @@ __global__ __launch_bounds__(256) void k_lme(NodeSrc ns, int64_t n_mp, const dou
                                              const int32_t* __restrict__ idx, int64_t cap,
                                              double beta, double tol, int max_iter,
                                              double* __restrict__ lam, double* __restrict__ N,
-                                             DN* __restrict__ dN, otm_diag* diag, Sink sink) {
+                                             DN* __restrict__ dN, otm_diag* diag, PairWindow other,
+                                             Sink sink) {
   constexpr int per_block = 256 / G;
   const int64_t p = (int64_t)xcd_block() * per_block + threadIdx.x / G;
   const int lane = threadIdx.x % G;
   if (p >= n_mp) return;  // whole group leaves together
-  if (offsets[n_mp] > cap) return;  // lists were not written (capacity)
+  const int64_t pairs = offsets[n_mp];
+  if (pairs > cap || other.holds(pairs)) return;  // lists were not written (capacity)
   const int K = (int)(offsets[p + 1] - offsets[p]);
   if (K <= G * PPL)
     lme_point<G, PPL, true, DN>(p, lane, ns, n_mp, xp, offsets, idx, cap, beta, tol,
@@ -480,8 +482,11 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
                                                  double beta, double tol, int max_iter,
                                                  double* __restrict__ lam,
                                                  double* __restrict__ N, DN* __restrict__ dN,
-                                                 otm_diag* diag, AsmIn a, int64_t chunk) {
+                                                 otm_diag* diag, PairWindow other, AsmIn a,
+                                                 int64_t chunk) {
   constexpr int per_round = 256 / G;
+  const int64_t pairs = offsets[n_mp];
+  if (other.holds(pairs)) return;
   const int64_t rpc = (chunk + per_round - 1) / per_round;  // rounds per chunk
   using Sink = AsmSink<DN, HEAT, Q>;
   __shared__ NodeTableV<Sink::V> table;
@@ -497,7 +502,7 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
   const int64_t n_chunks = (n_mp + chunk - 1) / chunk;
   const int64_t xcd = blockIdx.x % 8u, wgs = gridDim.x / 8u, j = blockIdx.x / 8u;
   const int64_t c_lo = n_chunks * xcd / 8, c_hi = n_chunks * (xcd + 1) / 8;
-  const bool ok = offsets[n_mp] <= cap;  // lists were written (capacity)
+  const bool ok = pairs <= cap;  // lists were written (capacity)
   const int lane = tid % G;
   NodeDst<Sink::V> dst;
   dst.d[0] = a.m;
@@ -609,13 +614,45 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
   table_flush(table, tid, 256, dst);
 }
 
-// The pipelined kernel pays off from four rounds per workgroup on; below, its
-// first pass and its fixed grid cost more than the overlap gives.  It is for
-// OTM_FP64 alone: float32 values amplify a last-bit change of N or grad N (the
-// return map of OTM_MIXED turns it into 1e-6 of a point's stress, the storage
-// of OTM_MIXED_STORAGE into 6e-8 where it moves a value over a rounding
-// boundary), so their results keep this kernel's order of operations.
+// The pipelined kernel is for OTM_FP64 alone: float32 values amplify a last-bit
+// change of N or grad N (the return map of OTM_MIXED turns it into 1e-6 of a
+// point's stress, the storage of OTM_MIXED_STORAGE into 6e-8 where it moves a
+// value over a rounding boundary), so their results keep this kernel's order of
+// operations.  In OTM_FP64 it is the better one for bodies of enough rounds per
+// workgroup and rows of 24 (31) to 38 pairs on average:
+//  - Past 38, its rows past 40 pairs, solved from memory in a pass of their own,
+//    cost more than the overlap gives: 0.32M MPs with 39 pairs, assembling, from
+//    the last multiplier 490 us, 391 here; with 37 pairs 351, 425 here.
+//  - It always runs six pairs a lane, so that short rows pay for slots that they
+//    leave empty: with 16 pairs 163 us, 135 here (four lanes need up to five).
+//  - With 27 pairs it gains from 262144 MPs on (0.28M 183 us, 188 here; 1.13M 618,
+//    691; but 0.14M 109, 95: its first pass and its fixed grid), and with the
+//    segmented assembly, whose stores it overlaps, at every size (0.14M 274 us,
+//    284 here).  From 31 on, where many rows have more than the 36 pairs that are
+//    cached here, it gains at every size (0.14M MPs with 34.5 pairs 125 us, 136).
+//  - Calls without node records are stand-alone ones from a cold start, mostly,
+//    whose many evaluations leave nothing to overlap: with 27 pairs 0.45M MPs
+//    352 us, 350 here; 1.13M 828, 827.
+// The host knows the lists' capacity alone.  A step's is taken for 1.3 times its
+// pairs (the margin of the Python layer), a stand-alone call's for their number.
+// No mean is longer than the capacity over the MPs: past 38 of these both
+// kernels are launched, and the one whose rows they are not leaves at once
+// (that launch costs 5 us).
 constexpr int64_t kPipelinedMps = 4 * 512 * 64;
+struct LmeRoute {
+  PairWindow pipelined;  // none: the kernel of this file alone
+  bool sure;             // the pipelined kernel alone
+};
+static LmeRoute lme_route(int64_t n_nodes, int64_t n_mp, int64_t capacity, bool records,
+                          bool segmented) {
+  const LmeRoute here{{1, 0}, false};
+  if (n_mp < kPipelinedMps || n_nodes <= 0) return here;
+  const int64_t lo = segmented || (records && n_mp >= 2 * kPipelinedMps) ? 24 : 31, hi = 38;
+  const int64_t margin = records ? 13 : 10;  // tenths
+  if (10 * capacity < margin * lo * n_mp || 10 * capacity > margin * hi * n_mp) return here;
+  if (capacity <= hi * n_mp) return {{0, INT64_MAX}, true};
+  return {{lo * n_mp, hi * n_mp}, false};
+}
 
 void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const double* x_mp,
                 const int64_t* nbr_offsets, const int32_t* nbr_idx, int64_t pair_capacity,
@@ -623,11 +660,14 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
                 int32_t precision, const double4* packed, otm_diag* diag, hipStream_t s,
                 const AsmIn* fused, const SegIn* seg, bool kept) {
   if (n_mp <= 0) return;
-  if (precision == OTM_FP64 && n_mp >= kPipelinedMps) {
+  LmeRoute route{{1, 0}, false};
+  if (precision == OTM_FP64)
+    route = lme_route(n_nodes, n_mp, pair_capacity, packed != nullptr, seg != nullptr);
+  const PairWindow other = route.pipelined;
+  if (other.lo <= other.hi)
     launch_lme_pipelined(n_nodes, x_nodes, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
-                         tol, max_iter, lam, N, (double*)dN, packed, diag, s, fused, seg);
-    return;
-  }
+                         tol, max_iter, lam, N, (double*)dN, packed, diag, other, s, fused, seg);
+  if (route.sure) return;
   const NodeSrc ns{x_nodes, packed, n_nodes};
   constexpr int G = 4, PPL = 9;
   if (fused != nullptr) {
@@ -635,7 +675,7 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
     const int64_t chunk = lme_asm_chunk(n_mp);
     auto run = [&](auto kernel, auto* dn) {
       kernel<<<kLmeAsmBlocks, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity,
-                                           beta, tol, max_iter, lam, N, dn, diag, *fused, chunk);
+                                           beta, tol, max_iter, lam, N, dn, diag, other, *fused, chunk);
     };
     auto pick = [&](auto leave) {
       constexpr bool LEAVE = decltype(leave)::value;
@@ -663,7 +703,7 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
   const unsigned nb = (unsigned)((n_mp + (256 / G) - 1) / (256 / G));
   auto run = [&](auto sink, auto* dn) {
     k_lme<G, PPL><<<nb, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
-                                     tol, max_iter, lam, N, dn, diag, sink);
+                                     tol, max_iter, lam, N, dn, diag, other, sink);
   };
   if (precision == OTM_FP64) {
     if (seg != nullptr)

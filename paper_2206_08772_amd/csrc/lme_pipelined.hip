@@ -666,6 +666,7 @@ template <bool PACKED, class Sink>
 struct LmeCall {
   LmeArgs<PACKED> a;
   typename Sink::In in;
+  PairWindow mine;
   int chunk;
 };
 
@@ -684,7 +685,8 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
   __shared__ typename Sink::Table table;
   __shared__ __align__(16) double stage[4][kStage + 2];
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int64_t n_mp = call.a.n_mp;
+  const int64_t n_mp = call.a.n_mp, pairs = call.a.offsets[n_mp];
+  if (!call.mine.holds(pairs)) return;
   const int chunk = call.chunk;
   const int rpc = (chunk + kPerRound - 1) / kPerRound;  // rounds per chunk
   Sink sink;
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
   const int n_chunks = (int)((n_mp + chunk - 1) / chunk);
   const int xcd = blockIdx.x % 8u, wgs = gridDim.x / 8u;
   const int c_hi = (int)((int64_t)n_chunks * (xcd + 1) / 8);
-  const bool ok = call.a.offsets[n_mp] <= call.a.cap;  // lists were written (capacity)
+  const bool ok = pairs <= call.a.cap;  // lists were written (capacity)
   // Round k of chunk c, and its first MP.
   struct Place {
     int c, k;
@@ -790,7 +792,9 @@ __global__ __launch_bounds__(256, 2) void k_lme(LmeCall<PACKED, Sink> call) {
       e[k] = 0.0;
     }
     const Slots sl(lim);
-    const Solve res = lme_solve(d, e, sl, fits, c0.a.beta, c0.a.tol, c0.a.max_iter, lam, iz, Mi);
+    Solve res = Solve::Leave;
+    if (__ballot(fits) != 0)  // (the first pass, and waves of long rows, have none)
+      res = lme_solve(d, e, sl, fits, c0.a.beta, c0.a.tol, c0.a.max_iter, lam, iz, Mi);
     places();
     const Call& c1 = kernel_arg<Call>();
     const bool add = res != Solve::Leave;
@@ -930,24 +934,18 @@ struct Type {
 void launch_lme_pipelined(int64_t n_nodes, const double* x_nodes, int64_t n_mp,
                           const double* x_mp, const int64_t* nbr_offsets, const int32_t* nbr_idx,
                           int64_t pair_capacity, double beta, double tol, int32_t max_iter,
-                          double* lam, double* N, double* dN, const double4* packed, otm_diag* diag, hipStream_t s,
-                          const AsmIn* fused, const SegIn* seg) {
+                          double* lam, double* N, double* dN, const double4* packed,
+                          otm_diag* diag, PairWindow mine, hipStream_t s, const AsmIn* fused,
+                          const SegIn* seg) {
   if (n_mp <= 0) return;
   const int chunk = lme_chunk(n_mp);
-  // without nodes or pairs every row is empty; the loads that stand in for a
-  // missing row then read these
-  if (n_nodes <= 0) {
-    x_nodes = x_mp;
-    if (packed != nullptr) packed = (const double4*)x_mp;
-  }
-  if (pair_capacity <= 0) nbr_idx = (const int32_t*)nbr_offsets;
   auto run = [&](auto tag, auto pk, auto in) {
     using Sink = typename decltype(tag)::type;
     constexpr bool PACKED = decltype(pk)::value;
     const LmeCall<PACKED, Sink> call{
         LmeArgs<PACKED>{NodeSrc<PACKED>{x_nodes, packed, n_nodes}, n_mp, x_mp, nbr_offsets,
                         nbr_idx, pair_capacity, beta, tol, max_iter, lam, N, dN, diag},
-        in, chunk};
+        in, mine, chunk};
     k_lme<PACKED, Sink><<<kLmeBlocks, 256, 0, s>>>(call);
   };
   // (the step's calls, the ones with a sink, always bring node records)
