@@ -247,9 +247,11 @@ OTM_DEV double rsqrt_refined(double x) {
 OTM_DEV void jacobi_angle_fp64(double app, double aqq, double apq, double& t, double& c,
                                double& sn) {
   double a = aqq - app, b = 2.0 * apq;
-  if (fabs(a) + fabs(b) < 1e-140) {  // the squares would underflow
-    a *= 0x1p500;
-    b *= 0x1p500;
+  const double size = fabs(a) + fabs(b);
+  if (!(size >= 1e-140 && size <= 1e140)) {  // the squares would leave the range
+    const double k = size < 1.0 ? 0x1p500 : 0x1p-600;
+    a *= k;
+    b *= k;
   }
   const double y = rsqrt_refined(fma(a, a, b * b));
   const double c2 = fma(0.5 * fabs(a), y, 0.5);
