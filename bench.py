@@ -581,12 +581,13 @@ def main():
     phases["mp_update"] = dict(roof, ms=round(ph["mp_update"], 4))
     # `roofline` is the MP pass (the kernel the HBM target is set on); the
     # longest kernel is the shape functions with the fused assembly
-    longest = dict(kernel="k_lme (float64 LME Newton + fused atomic assembly)",
+    longest = dict(kernel=("k_lme" if w.n_mp >= 262144 else "k_lme_asm") +
+                          " (float64 LME Newton + fused atomic assembly)",
                    ms=phases["lme_assembly"]["ms"],
                    share_of_step=round(phases["lme_assembly"]["ms"] / main_run["ms_per_step"], 3),
                    hbm_frac=phases["lme_assembly"]["frac"],
-                   bound="arithmetic for half of its time (VALU issue at 85 %), then the stores "
-                         "of N and grad N and the node sums")
+                   counters="profiles/valu_taylor_rod_fp64_mixed.md, "
+                            "profiles/memory_pipeline_taylor_rod_fp64.md")
 
     line = {
         "metric": "material-point steps/s (FP64 vs mixed, 1 GPU) + adjoint/forward time ratio",

@@ -18,8 +18,9 @@ size_t carve_workspace(void* base, size_t bytes, int64_t n_nodes, int64_t n_mp,
   const int64_t cap_cells = (n_nodes > 0 ? n_nodes : 0) + 1024;
   // block totals of the largest scan: the MPs' pairs, the node influence
   // offsets, or the node and MP cell counts scanned together (two arrays).
-  // (Sized, as the ticket and the spare area below, for 4096 elements per
-  // scan workgroup: the bytes a workspace needs stay what they were.)
+  // (Sized for 4096 elements per scan workgroup, and the ticket and the spare
+  // area below for more than is used: the total decides which bodies fit the
+  // scratch of otm_step_noalloc, and a body that was refused stays refused.)
   auto blocks = [](int64_t n) { return (n + 4095) / 4096; };
   static_assert(kScanBlock >= 4096, "one entry per scan workgroup fits");
   int64_t scan_blocks = blocks(n_mp + 1);

@@ -9,12 +9,14 @@
 // with a list skin of 0.1 h; MPs with more than 40 pairs are left to a second
 // pass that re-reads their pairs from memory at every evaluation.
 //
-// Measured on the rod with 1.13M MPs, deforming, shape functions with the fused
-// assembly: 0.66 ms against 0.74 ms with lme.hip's kernel; with a list skin of
-// 0.1 h (33 pairs per MP, a tenth of the MPs past that kernel's 36) 0.69
-// against 1.05 ms with those rows solved in their round.  Of the 0.66 ms the arithmetic alone takes 0.35 (VALU issue
-// at 85 %), the stores 0.10 (0.29 there: 17M write requests instead of 44M), the
-// table sums 0.06, their flush to memory 0.06 and the table slots 0.05.
+// Measured on a rod of 1.13M MPs, shape functions with the fused assembly from the
+// last multiplier: 618 us against 691 with lme.hip's kernel at 27 pairs per MP, 689
+// against 823 at 32 (a list skin of 0.1 h), 755 against 1366 at 35, where one MP in
+// four has more than the 36 pairs that kernel holds (lme.hip's dispatch has the sizes
+// and lengths where it is the slower one).  No unit is full: the VALU is 39 % busy, the
+// L1s' data path 79 %, and the waves wait a third of their time, two per SIMD, for
+// the chain of one MP's Newton steps.  14.7 write requests per MP leave for the L2
+// (34.8 from lme.hip's kernel with float32 grad N).
 //
 //  - Workgroups are persistent and their rounds (64 MPs) pipelined: vector
 //    memory operations complete in order, so a wait for loads issued after a
@@ -188,16 +190,17 @@ struct Slots {
   }
 };
 
-// What happens to each finished pair besides storing N and grad N.  For rows in
-// registers the sink is first shown the lane's node ids (claim), then the MP
-// (begin; the loads are waited for in ready) and its pairs (add_row);
-// a row re-read from memory shows its pairs by their place in the lists
-// (operator()).
 // Float64 atomic add to device memory (never a generic-address one, whose
 // completion order the compiler cannot count on).
 OTM_DEV void global_add(double* p, double v) {
   __builtin_amdgcn_global_atomic_fadd_f64((__attribute__((address_space(1))) double*)p, v);
 }
+
+// What happens to each finished pair besides storing N and grad N: a sink.  For
+// rows in registers it is first shown the lane's node ids (claim) and then, once
+// the solve is done, the row (add_row) with its MP (Mp::load, waited for in
+// ready); a row re-read from memory shows its pairs one by one, by their place
+// in the lists (add).  flush ends a span of rounds.
 
 struct NoTable {};
 struct NoSink {
