@@ -691,12 +691,14 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
         else run(k_lme_asm<G, PPL, LEAVE, float, false, double>, (float*)dN);
       }
     };
-    // Lists kept over steps carry a skin, and with it many rows past G * PPL
-    // pairs (one in ten at 0.1 h: nearly every wave has one), which are then
-    // left to the packed pass: 0.55M MPs 381 us, 535 in place.  Lists of the
+    // Lists kept over steps carry a skin as a rule, and with it many rows past
+    // G * PPL pairs (one in ten at 0.1 h: nearly every wave has one), which are
+    // then left to the packed pass: 0.55M MPs 381 us, 535 in place.  Lists of the
     // step's own radius have next to none, and the code that leaves them costs
-    // the other rows 1.4 % (1.13M MPs 646 us, 637 in place).
-    if (kept) pick(std::true_type{});
+    // the other rows 1.4 % (1.13M MPs 646 us, 637 in place; steps of 0.28M with
+    // kept lists 248 us in OTM_MIXED, 243 in place): they are told by a capacity
+    // of up to 38 pairs per MP (lme_route's 1.3 times 29).
+    if (kept && pair_capacity > 38 * n_mp) pick(std::true_type{});
     else pick(std::false_type{});
     return;
   }
