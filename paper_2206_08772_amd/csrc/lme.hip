@@ -430,20 +430,22 @@ OTM_DEV void lme_point(int64_t p, int lane, const NodeSrc& ns, int64_t n_mp, con
   }
 }
 
-template <int G, int PPL, typename DN, class Sink>
+// ASK: lists of ``other`` pairs in all are the other kernel's.
+template <int G, int PPL, bool ASK, typename DN, class Sink>
 __global__ __launch_bounds__(256) void k_lme(NodeSrc ns, int64_t n_mp, const double* __restrict__ xp,
                                              const int64_t* __restrict__ offsets,
                                              const int32_t* __restrict__ idx, int64_t cap,
                                              double beta, double tol, int max_iter,
                                              double* __restrict__ lam, double* __restrict__ N,
-                                             DN* __restrict__ dN, otm_diag* diag, PairWindow other,
-                                             Sink sink) {
+                                             DN* __restrict__ dN, otm_diag* diag, Sink sink,
+                                             PairWindow other) {
   constexpr int per_block = 256 / G;
   const int64_t p = (int64_t)xcd_block() * per_block + threadIdx.x / G;
   const int lane = threadIdx.x % G;
   if (p >= n_mp) return;  // whole group leaves together
-  const int64_t pairs = offsets[n_mp];
-  if (pairs > cap || other.holds(pairs)) return;  // lists were not written (capacity)
+  if (offsets[n_mp] > cap) return;  // lists were not written (capacity)
+  if constexpr (ASK)
+    if (other.holds(offsets[n_mp])) return;
   const int K = (int)(offsets[p + 1] - offsets[p]);
   if (K <= G * PPL)
     lme_point<G, PPL, true, DN>(p, lane, ns, n_mp, xp, offsets, idx, cap, beta, tol,
@@ -460,7 +462,8 @@ __global__ __launch_bounds__(256) void k_lme(NodeSrc ns, int64_t n_mp, const dou
 // to m and f every kLmeAsmFlushRounds rounds and at the end of each chunk.
 // The round count is the same for every lane of a workgroup, so the barriers
 // around a flush are reached by all of them.  Rows of more than G * PPL pairs
-// take the uncached solve in their round, or (LEAVE) after the last one.
+// take the uncached solve in their round, or (LEAVE) after the last one.  ASK: as
+// for k_lme.
 constexpr int kLmeAsmBlocks = 512;
 constexpr int kLmeAsmFlushRounds = 8;
 static_assert(kLmeAsmBlocks % 8 == 0, "the workgroups split evenly over the 8 XCDs");
@@ -474,7 +477,7 @@ inline int64_t lme_asm_chunk(int64_t n_mp) {
   return per_wg >= 4 * 512 ? 512 : per_wg;
 }
 
-template <int G, int PPL, bool LEAVE, typename DN, bool HEAT, typename Q>
+template <int G, int PPL, bool LEAVE, typename DN, bool HEAT, typename Q, bool ASK>
 __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
                                                  const double* __restrict__ xp,
                                                  const int64_t* __restrict__ offsets,
@@ -482,11 +485,11 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
                                                  double beta, double tol, int max_iter,
                                                  double* __restrict__ lam,
                                                  double* __restrict__ N, DN* __restrict__ dN,
-                                                 otm_diag* diag, PairWindow other, AsmIn a,
-                                                 int64_t chunk) {
+                                                 otm_diag* diag, AsmIn a, int64_t chunk,
+                                                 PairWindow other) {
   constexpr int per_round = 256 / G;
-  const int64_t pairs = offsets[n_mp];
-  if (other.holds(pairs)) return;
+  if constexpr (ASK)
+    if (other.holds(offsets[n_mp])) return;
   const int64_t rpc = (chunk + per_round - 1) / per_round;  // rounds per chunk
   using Sink = AsmSink<DN, HEAT, Q>;
   __shared__ NodeTableV<Sink::V> table;
@@ -502,7 +505,7 @@ __global__ __launch_bounds__(256) void k_lme_asm(NodeSrc ns, int64_t n_mp,
   const int64_t n_chunks = (n_mp + chunk - 1) / chunk;
   const int64_t xcd = blockIdx.x % 8u, wgs = gridDim.x / 8u, j = blockIdx.x / 8u;
   const int64_t c_lo = n_chunks * xcd / 8, c_hi = n_chunks * (xcd + 1) / 8;
-  const bool ok = pairs <= cap;  // lists were written (capacity)
+  const bool ok = offsets[n_mp] <= cap;  // lists were written (capacity)
   const int lane = tid % G;
   NodeDst<Sink::V> dst;
   dst.d[0] = a.m;
@@ -664,7 +667,8 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
   if (precision == OTM_FP64)
     route = lme_route(n_nodes, n_mp, pair_capacity, packed != nullptr, seg != nullptr);
   const PairWindow other = route.pipelined;
-  if (other.lo <= other.hi)
+  const bool ask = other.lo <= other.hi;  // both kernels, unless it is sure
+  if (ask)
     launch_lme_pipelined(n_nodes, x_nodes, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
                          tol, max_iter, lam, N, (double*)dN, packed, diag, other, s, fused, seg);
   if (route.sure) return;
@@ -675,20 +679,25 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
     const int64_t chunk = lme_asm_chunk(n_mp);
     auto run = [&](auto kernel, auto* dn) {
       kernel<<<kLmeAsmBlocks, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity,
-                                           beta, tol, max_iter, lam, N, dn, diag, other, *fused, chunk);
+                                           beta, tol, max_iter, lam, N, dn, diag, *fused, chunk, other);
     };
     auto pick = [&](auto leave) {
       constexpr bool LEAVE = decltype(leave)::value;
       const bool heat = fused->heat != nullptr;
+      auto fp64 = [&](auto ask) {
+        constexpr bool ASK = decltype(ask)::value;
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, double, true, double, ASK>, (double*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, double, false, double, ASK>, (double*)dN);
+      };
       if (precision == OTM_FP64) {
-        if (heat) run(k_lme_asm<G, PPL, LEAVE, double, true, double>, (double*)dN);
-        else run(k_lme_asm<G, PPL, LEAVE, double, false, double>, (double*)dN);
+        if (ask) fp64(std::true_type{});
+        else fp64(std::false_type{});
       } else if (precision == OTM_MIXED) {
-        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, float>, (float*)dN);
-        else run(k_lme_asm<G, PPL, LEAVE, float, false, float>, (float*)dN);
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, float, false>, (float*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, float, false, float, false>, (float*)dN);
       } else {
-        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, double>, (float*)dN);
-        else run(k_lme_asm<G, PPL, LEAVE, float, false, double>, (float*)dN);
+        if (heat) run(k_lme_asm<G, PPL, LEAVE, float, true, double, false>, (float*)dN);
+        else run(k_lme_asm<G, PPL, LEAVE, float, false, double, false>, (float*)dN);
       }
     };
     // Lists kept over steps carry a skin as a rule, and with it many rows past
@@ -704,8 +713,11 @@ void launch_lme(int64_t n_nodes, const double* x_nodes, int64_t n_mp, const doub
   }
   const unsigned nb = (unsigned)((n_mp + (256 / G) - 1) / (256 / G));
   auto run = [&](auto sink, auto* dn) {
-    k_lme<G, PPL><<<nb, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta,
-                                     tol, max_iter, lam, N, dn, diag, other, sink);
+    auto kernel = k_lme<G, PPL, false, std::remove_pointer_t<decltype(dn)>, decltype(sink)>;
+    if constexpr (std::is_same_v<decltype(dn), double*>)
+      if (ask) kernel = k_lme<G, PPL, true, double, decltype(sink)>;
+    kernel<<<nb, 256, 0, s>>>(ns, n_mp, x_mp, nbr_offsets, nbr_idx, pair_capacity, beta, tol,
+                              max_iter, lam, N, dn, diag, sink, other);
   };
   if (precision == OTM_FP64) {
     if (seg != nullptr)
