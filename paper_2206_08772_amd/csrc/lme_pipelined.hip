@@ -14,7 +14,7 @@
 // against 823 at 32 (a list skin of 0.1 h), 755 against 1366 at 35, where one MP in
 // four has more than the 36 pairs that kernel holds (lme.hip's dispatch has the sizes
 // and lengths where it is the slower one).  No unit is full: the VALU is 39 % busy, the
-// L1s' data path 79 %, and the waves wait a third of their time, two per SIMD, for
+// L1s' data path 80 %, and the waves wait a third of their time, two per SIMD, for
 // the chain of one MP's Newton steps.  14.7 write requests per MP leave for the L2
 // (34.8 from lme.hip's kernel with float32 grad N).
 //
